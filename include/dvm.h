@@ -413,7 +413,7 @@ void dvm_destroy_batch(dvm_batch *b);
  * then the standardisation mean[10] and std[10] (x_std = (x - mean) / std).
  * dvm_mlp_create / dvm_mlp_workspace_bytes / dvm_mlp_bind -- host object for
  * batches of up to max_batch samples; the workspace (caller-owned, device)
- * holds the Adam moments, the gradients and per-sample scratch.  Binding
+ * holds the Adam moments, the gradients and the workgroups' partial sums.  Binding
  * resets the Adam state (the caller's workspace must be zero-filled).
  * dvm_mlp_set_normalization -- mean and standard deviation of x[n][10]
  * (FP64, fixed order) into the parameter block.
@@ -422,7 +422,7 @@ void dvm_destroy_batch(dvm_batch *b);
  * FP32 accumulation; the one the sensor uses).
  * dvm_mlp_gradient -- loss and weight gradients of the class-weighted
  * binary cross-entropy mean_i w_i [softplus(z_i) - y_i z_i], w_i = pos_weight
- * for y_i = 1, else 1 (FP32 forward/backward, FP64 sums in sample order).
+ * for y_i = 1, else 1 (FP32 forward/backward, FP64 sums in a fixed order).
  * dvm_mlp_adam -- one Adam step (beta 0.9, 0.999, eps 1e-8, bias-corrected)
  * from the last gradients.  dvm_mlp_train_step = gradient + Adam.
  * dvm_mlp_buffers -- device pointers of the last gradients [DVM_MLP_WEIGHTS]
@@ -476,10 +476,9 @@ int dvm_mlp_buffers(const dvm_mlp *net, const float **grads, const double **loss
  * serving loops): the loss and weight gradients of dvm_mlp_gradient, written
  * to the caller's grad[DVM_MLP_WEIGHTS] (FP32, device) and *loss (FP64,
  * device), from the parameter block params[DVM_MLP_PARAMS] (device).  No
- * network object, no workspace: the per-sample scratch lives in a static
- * device array of the library, one per GPU, sized for
- * DVM_NOALLOC_MAX_BATCH samples (about 10.4 MiB, held until the process
- * ends).  n outside [1, DVM_NOALLOC_MAX_BATCH] is DVM_ERR_WORKSPACE.  Same
+ * network object, no workspace: the workgroups' partial sums live in a
+ * static device array of the library, one per GPU (about 9.7 MiB, held until
+ * the process ends).  n outside [1, DVM_NOALLOC_MAX_BATCH] is DVM_ERR_WORKSPACE.  Same
  * kernels as dvm_mlp_gradient, so the same result bitwise.  Every call on a
  * GPU shares that scratch: calls that overlap on one GPU (other streams,
  * other host threads) race and must be serialised by the caller.  Calls no

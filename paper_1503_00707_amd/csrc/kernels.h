@@ -104,14 +104,24 @@ struct HybArgsPub {
     int32_t closed;  // fluid-fluid faces: continuous half-range integrals
     int32_t pad;
 };
-constexpr int kMlpParams = 4949, kMlpWeights = 4929, kMlpRecord = 331, kFluxRecord = 71, kFaceRecord = 30;
+constexpr int kMlpParams = 4949, kMlpWeights = 4929, kFluxRecord = 71, kFaceRecord = 30;
 hipError_t launch_features(const SensorArgsPub &a, float *x, hipStream_t st);
 hipError_t launch_labels(bool fp64, const void *f, float *r, int64_t n, const VelGrid &g, hipStream_t st);
 hipError_t launch_mlp_forward(const float *params, const float *x, int64_t n, int mode, float *z, hipStream_t st);
 hipError_t launch_sensor(const SensorArgsPub &a, const float *params, double kappa, uint8_t *mask, float *score,
                          hipStream_t st);
+// Workgroups of a training launch: one per tile of 16 samples up to
+// kTrainBlocks (each leaves kMlpWeights FP64 sums to be added up, so more of
+// them than compute units only adds traffic).
+constexpr int kTrainBlocks = 256;
+inline int train_blocks(int64_t n) { return int(n < 16 * int64_t(kTrainBlocks) ? (n + 15) / 16 : kTrainBlocks); }
+// part [train_blocks(n)][kMlpWeights], loss_part [train_blocks(n)]
 hipError_t launch_train(const float *params, const float *x, const float *y, int64_t n, float pos_weight,
-                        float *rec, double *loss_part, float *grad, double *loss, hipStream_t st);
+                        double *part, double *loss_part, float *grad, double *loss, hipStream_t st);
+// the same and the Adam update of the weights from that gradient
+hipError_t launch_train_adam(float *params, const float *x, const float *y, int64_t n, float pos_weight,
+                             double *part, double *loss_part, float *grad, double *loss, float *m, float *v, float lr,
+                             float c1, float c2, hipStream_t st);
 hipError_t launch_adam(float *params, float *m, float *v, const float *grad, float lr, float c1, float c2,
                        hipStream_t st);
 // launch_train with its scratch in a static device array (no allocation)

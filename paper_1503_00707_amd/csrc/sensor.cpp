@@ -79,8 +79,9 @@ int dvm_mlp_create(int64_t max_batch, dvm_mlp **out) {
     net->off_v = o;     o += align256(kMlpWeights * sizeof(float));
     net->off_grad = o;  o += align256(kMlpWeights * sizeof(float));
     net->off_loss = o;  o += 256;
-    net->off_lpart = o; o += align256(size_t((max_batch + 255) / 256) * sizeof(double));
-    net->off_rec = o;   o += align256(size_t(max_batch) * kMlpRecord * sizeof(float));
+    const size_t nb = size_t(train_blocks(max_batch));
+    net->off_lpart = o; o += align256(nb * sizeof(double));
+    net->off_part = o;  o += align256(nb * kMlpWeights * sizeof(double));
     net->ws_bytes = o;
     *out = net;
     return DVM_OK;
@@ -123,7 +124,7 @@ int dvm_mlp_gradient(dvm_mlp *net, const float *x, const float *y, int64_t n, fl
     int rc = check_net(net, n);
     if (rc) return rc;
     if (!x || !y || !(pos_weight > 0)) return fail(DVM_ERR_ARG, "bad argument");
-    hipError_t e = launch_train(net->params, x, y, n, pos_weight, net->rec(), net->lpart(), net->grad(), net->loss(),
+    hipError_t e = launch_train(net->params, x, y, n, pos_weight, net->part(), net->lpart(), net->grad(), net->loss(),
                                 S(stream));
     return e == hipSuccess ? DVM_OK : hip_fail(e, "gradient");
 }
@@ -151,8 +152,23 @@ int dvm_mlp_adam(dvm_mlp *net, float lr, void *stream) {
 
 int dvm_mlp_train_step(dvm_mlp *net, const float *x, const float *y, int64_t n, float lr, float pos_weight,
                        void *stream) {
-    int rc = dvm_mlp_gradient(net, x, y, n, pos_weight, stream);
-    return rc ? rc : dvm_mlp_adam(net, lr, stream);
+    if (!(lr > 0)) {  // the gradient is taken all the same, then the learning rate refused
+        int rc = dvm_mlp_gradient(net, x, y, n, pos_weight, stream);
+        return rc ? rc : dvm_mlp_adam(net, lr, stream);
+    }
+    clear_error();
+    int rc = check_net(net, n);
+    if (rc) return rc;
+    if (!x || !y || !(pos_weight > 0)) return fail(DVM_ERR_ARG, "bad argument");
+    net->t++;
+    const double c1 = 1.0 - std::pow(0.9, double(net->t)), c2 = 1.0 - std::pow(0.999, double(net->t));
+    hipError_t e = launch_train_adam(net->params, x, y, n, pos_weight, net->part(), net->lpart(), net->grad(),
+                                     net->loss(), net->m(), net->v(), lr, float(c1), float(c2), S(stream));
+    if (e != hipSuccess) {
+        net->t--;
+        return hip_fail(e, "train step");
+    }
+    return DVM_OK;
 }
 
 int dvm_mlp_buffers(const dvm_mlp *net, const float **grads, const double **loss) {

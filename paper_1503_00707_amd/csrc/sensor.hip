@@ -8,16 +8,17 @@
 
 namespace dvm {
 
-// Static scratch of dvm_mlp_gradient_noalloc: the per-sample records and the
-// per-block loss partials of up to kNoAllocMaxBatch samples.  Each GPU holds
-// its own copy until the process ends; every call on a GPU shares it.
+// Static scratch of dvm_mlp_gradient_noalloc: the blocks' gradient sums and
+// loss partials (train_blocks is at most kTrainBlocks whatever the batch).
+// Each GPU holds its own copy until the process ends; every call on a GPU
+// shares it.
 namespace {
-constexpr size_t kScratchRec = (size_t(kNoAllocMaxBatch) * kMlpRecord * sizeof(float) + 255) & ~size_t(255);
-constexpr size_t kScratchPart = (size_t((kNoAllocMaxBatch + 255) / 256) * sizeof(double) + 255) & ~size_t(255);
+constexpr size_t kScratchGrad = (size_t(kTrainBlocks) * kMlpWeights * sizeof(double) + 255) & ~size_t(255);
+constexpr size_t kScratchLoss = (size_t(kTrainBlocks) * sizeof(double) + 255) & ~size_t(255);
 constexpr int kMaxDevices = 64;
 constexpr int64_t kSensorSmallMesh = 65536;
 }  // namespace
-static __device__ __align__(256) char scratch[kScratchRec + kScratchPart];
+static __device__ __align__(256) char scratch[kScratchGrad + kScratchLoss];
 
 // Device address of this GPU's scratch (the host-side name of the array is
 // not a device address): looked up once per device, with it current.
@@ -42,7 +43,7 @@ static hipError_t scratch_on_device(char **out) {
 static_assert(sizeof(SensorArgsPub) == sizeof(impl::FeatArgs), "argument layout");
 static_assert(sizeof(HybArgsPub) == sizeof(impl::HybArgs), "argument layout");
 static_assert(kMlpParams == impl::kParams && kMlpWeights == impl::kWeights, "parameter block");
-static_assert(kMlpRecord == impl::kRec && kFluxRecord == impl::kFluxRec, "scratch records");
+static_assert(kFluxRecord == impl::kFluxRec, "flux records");
 static_assert(kFaceRecord == 6 * 5, "face flux records");
 
 static impl::FeatArgs feat(const SensorArgsPub &a) {
@@ -80,15 +81,29 @@ hipError_t launch_sensor(const SensorArgsPub &a, const float *params, double kap
     return hipGetLastError();
 }
 
-hipError_t launch_train(const float *params, const float *x, const float *y, int64_t n, float pos_weight,
-                        float *rec, double *loss_part, float *grad, double *loss, hipStream_t st) {
-    const unsigned nb = unsigned((n + 255) / 256);
-    hipLaunchKernelGGL(impl::k_train_fb, dim3(nb), dim3(256), 0, st, params, x, y, n, pos_weight, rec, loss_part);
+static hipError_t train(const float *params, const float *x, const float *y, int64_t n, float pos_weight,
+                        double *part, double *loss_part, float *grad, double *loss, const impl::AdamArgs &adam,
+                        hipStream_t st) {
+    const int nb = train_blocks(n);
+    hipLaunchKernelGGL(impl::k_train_tiles, dim3(unsigned(nb)), dim3(256), 0, st, params, x, y, n, pos_weight, part,
+                       loss_part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(impl::k_train_grads, dim3(unsigned((impl::kWeights + 255) / 256)), dim3(256), 0, st, rec, n,
-                       loss_part, int(nb), grad, loss);
+    hipLaunchKernelGGL(impl::k_train_reduce, dim3(unsigned((impl::kWeights + 63) / 64)), dim3(256), 0, st, part,
+                       loss_part, nb, n, grad, loss, adam);
     return hipGetLastError();
+}
+
+hipError_t launch_train(const float *params, const float *x, const float *y, int64_t n, float pos_weight,
+                        double *part, double *loss_part, float *grad, double *loss, hipStream_t st) {
+    return train(params, x, y, n, pos_weight, part, loss_part, grad, loss, impl::AdamArgs{}, st);
+}
+
+hipError_t launch_train_adam(float *params, const float *x, const float *y, int64_t n, float pos_weight,
+                             double *part, double *loss_part, float *grad, double *loss, float *m, float *v, float lr,
+                             float c1, float c2, hipStream_t st) {
+    return train(params, x, y, n, pos_weight, part, loss_part, grad, loss, impl::AdamArgs{params, m, v, lr, c1, c2},
+                 st);
 }
 
 hipError_t launch_train_noalloc(const float *params, const float *x, const float *y, int64_t n, float pos_weight,
@@ -97,16 +112,16 @@ hipError_t launch_train_noalloc(const float *params, const float *x, const float
     char *base = nullptr;
     hipError_t e = scratch_on_device(&base);
     if (e != hipSuccess) return e;
-    // every record and partial the gradient kernel reads is written first by
-    // the forward/backward kernel of the same call: nothing to clear
-    return launch_train(params, x, y, n, pos_weight, reinterpret_cast<float *>(base),
-                        reinterpret_cast<double *>(base + kScratchRec), grad, loss, st);
+    // every sum and partial the reduction reads is written first by the tiles'
+    // kernel of the same call: nothing to clear
+    return launch_train(params, x, y, n, pos_weight, reinterpret_cast<double *>(base),
+                        reinterpret_cast<double *>(base + kScratchGrad), grad, loss, st);
 }
 
 hipError_t launch_adam(float *params, float *m, float *v, const float *grad, float lr, float c1, float c2,
                        hipStream_t st) {
-    hipLaunchKernelGGL(impl::k_adam, dim3(unsigned((impl::kWeights + 255) / 256)), dim3(256), 0, st, params, m, v,
-                       grad, lr, c1, c2);
+    hipLaunchKernelGGL(impl::k_adam, dim3(unsigned((impl::kWeights + 255) / 256)), dim3(256), 0, st,
+                       impl::AdamArgs{params, m, v, lr, c1, c2}, grad);
     return hipGetLastError();
 }
 

@@ -12,10 +12,10 @@
 // on the matrix cores: each wave pushes 16 cells through
 // v_mfma_f32_16x16x16_bf16 (BF16 weights and activations, FP32 accumulation).
 //
-// Training.  FP32 master weights; one thread per sample for the forward and
-// backward pass (activations and their GELU derivatives kept in a scratch
-// block), weight gradients summed in FP64 in sample order (deterministic),
-// then Adam.  Loss: class-weighted binary cross-entropy on the logit.
+// Training.  FP32 master weights; forward and backward pass in FP32 and the
+// weight gradients' sums over samples in FP64, tiles of 16 samples on the
+// matrix cores in a fixed order (deterministic), then Adam.  Loss:
+// class-weighted binary cross-entropy on the logit.
 //
 // Hybrid step (paper: kinetic and continuum cells on one adaptive mesh).  A
 // frozen mask per step: kinetic cells run the fused DVM step unchanged;
@@ -373,104 +373,186 @@ __global__ __launch_bounds__(4 * R) void k_sensor(FeatArgs a, const float *P, do
 // training
 // ---------------------------------------------------------------------------
 
-// per-sample scratch record (floats)
-constexpr int kRx = 0, kRh1 = kRx + kIn, kRg1 = kRh1 + kHid, kRh2 = kRg1 + kHid, kRd1 = kRh2 + kHid;
-constexpr int kRd2 = kRd1 + kHid, kRdz = kRd2 + kHid, kRec = kRdz + 1;
+typedef double f64x4 __attribute__((ext_vector_type(4)));
 
-// forward and backward of one sample per thread; block partial losses
-__global__ __launch_bounds__(256) void k_train_fb(const float *P, const float *x, const float *y, int64_t n,
-                                                  float pos_weight, float *rec, double *loss_part) {
-    __shared__ float w[kParams];
-    __shared__ double red[4];
-    for (int i = threadIdx.x; i < kParams; i += 256) w[i] = P[i];
-    __syncthreads();
-    const int64_t s = int64_t(blockIdx.x) * 256 + threadIdx.x;
-    double loss = 0.0;
-    if (s < n) {
-        float *R = rec + s * kRec;
-        for (int k = 0; k < kIn; ++k) R[kRx + k] = (x[s * kIn + k] - w[kMean + k]) / w[kStd + k];
-        for (int j = 0; j < kHid; ++j) {
-            float z = w[kB1 + j];
-            for (int k = 0; k < kIn; ++k) z += w[kW1 + j * kIn + k] * R[kRx + k];
-            R[kRh1 + j] = gelu_f(z);
-            R[kRg1 + j] = gelu_d(z);
-        }
-        float zo = w[kB3];
-        for (int j = 0; j < kHid; ++j) {
-            float z = w[kB2 + j];
-            for (int k = 0; k < kHid; ++k) z += w[kW2 + j * kHid + k] * R[kRh1 + k];
-            R[kRh2 + j] = gelu_f(z);
-            R[kRd2 + j] = gelu_d(z);  // derivative for now, delta below
-            zo += w[kW3 + j] * R[kRh2 + j];
-        }
-        const float yy = y[s];
-        const float wt = yy > 0.5f ? pos_weight : 1.0f;
-        const float ez = expf(-fabsf(zo));
-        const float sig = zo >= 0.0f ? 1.0f / (1.0f + ez) : ez / (1.0f + ez);
-        loss = double(wt) * (double(fmaxf(zo, 0.0f)) - double(zo) * yy + log1p(double(ez)));
-        const float dz = wt * (sig - yy) / float(n);
-        R[kRdz] = dz;
-        for (int j = 0; j < kHid; ++j) R[kRd2 + j] = dz * w[kW3 + j] * R[kRd2 + j];
-        for (int k = 0; k < kHid; ++k) {
-            float acc = 0.0f;
-            for (int j = 0; j < kHid; ++j) acc += R[kRd2 + j] * w[kW2 + j * kHid + k];
-            R[kRd1 + k] = acc * R[kRg1 + k];
-        }
-    }
-    double v[1] = {loss};
-    block_sum<256, 1>(v, red);
-    if (threadIdx.x == 0) loss_part[blockIdx.x] = v[0];
+// one weight of Adam with bias correction; c1 = 1 - beta1^t, c2 = 1 - beta2^t
+struct AdamArgs {
+    float *P, *m, *v;  // P NULL: the gradient only
+    float lr, c1, c2;
+};
+__device__ __forceinline__ void adam_one(const AdamArgs &a, int i, float g) {
+    const float mi = 0.9f * a.m[i] + 0.1f * g;
+    const float vi = 0.999f * a.v[i] + 0.001f * g * g;
+    a.m[i] = mi;
+    a.v[i] = vi;
+    a.P[i] -= a.lr * (mi / a.c1) / (sqrtf(vi / a.c2) + 1e-8f);
 }
 
-// weight gradients (FP64 sums in sample order) and the mean loss
-__global__ __launch_bounds__(256) void k_train_grads(const float *rec, int64_t n, const double *loss_part, int nlp,
-                                                     float *grad, double *loss) {
-    const int i = int(blockIdx.x) * 256 + threadIdx.x;
-    if (i == 0) {
+// Forward, backward and weight-gradient sums of tiles of 16 samples, one tile
+// at a time per workgroup of four waves (tile b, b + gridDim.x, ...); wave w
+// owns columns 16 w .. 16 w + 15 of both hidden layers.  All three 64-wide
+// contractions run on the matrix cores at the precision of the scalar code
+// they replace: the layers and the back-propagated deltas in FP32
+// (v_mfma_f32_16x16x4_f32), the gradient sums over samples in FP64
+// (v_mfma_f64_16x16x4_f64: products of two FP32 values are exact there).
+// Operand layouts for lane l, g = l / 16: A[l % 16][g], B[g][l % 16]; results:
+// FP32 D[4 g + v][l % 16], FP64 D[g + 4 v][l % 16].  The sums start from the
+// bias and take the inputs in index order, one fused multiply-add each, as a
+// scalar loop does.
+// part[block][kWeights]: the block's gradient sums; loss_part[block].
+// Bound: the latency of one tile (LDS round trips between the layers, erff and
+// expf), so as many workgroups as tiles up to kTrainBlocks.  A train step of
+// 4,096 samples: 2,053 us with one thread per sample, its activations in a
+// record in memory and one thread per weight summing over the samples; 19.7 us
+// with the two launches here.
+__global__ __launch_bounds__(256) void k_train_tiles(const float *P, const float *x, const float *y, int64_t n,
+                                                     float pos_weight, double *part, double *loss_part) {
+    constexpr int LD = kHid + 4;  // LDS row stride: 16-byte aligned rows on different banks
+    __shared__ __align__(16) float xs[16][16], h1[16][LD], h2[16][LD], d1[16][LD], d2[16][LD];
+    __shared__ float w3s[kHid], dz[16];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, li = lane & 15, g = lane >> 4;
+    const int j = 16 * wv + li;  // this lane's column
+    // the weights this lane multiplies by, kept for every tile
+    float b1w[3], b2w[16], b2t[16];
+#pragma unroll
+    for (int t = 0; t < 3; ++t) b1w[t] = 4 * t + g < kIn ? P[kW1 + j * kIn + 4 * t + g] : 0.0f;
+#pragma unroll
+    for (int t = 0; t < 16; ++t) {
+        b2w[t] = P[kW2 + j * kHid + 4 * t + g];
+        b2t[t] = P[kW2 + (4 * t + g) * kHid + j];
+    }
+    const float bias1 = P[kB1 + j], bias2 = P[kB2 + j], w3 = P[kW3 + j], b3 = P[kB3];
+    if (tid < kHid) w3s[tid] = P[kW3 + tid];
+    f64x4 a1 = {0, 0, 0, 0}, a2[4];  // gradient sums: w1 and b1 (column kIn), w2
+#pragma unroll
+    for (int nb = 0; nb < 4; ++nb) a2[nb] = f64x4{0, 0, 0, 0};
+    double av = 0.0, loss = 0.0;  // threads 0..63: b2; 64..127: w3; 128: b3
+    for (int64_t s0 = int64_t(blockIdx.x) * 16; s0 < n; s0 += int64_t(gridDim.x) * 16) {
+        const int nr = int(min(int64_t(16), n - s0));
+        {
+            const int r = tid >> 4, k = tid & 15;  // column kIn: one, for the bias gradients
+            float v = 0.0f;
+            if (r < nr) v = k < kIn ? (x[(s0 + r) * kIn + k] - P[kMean + k]) / P[kStd + k] : k == kIn ? 1.0f : 0.0f;
+            xs[r][k] = v;
+        }
+        __syncthreads();
+        f32x4 z = {bias1, bias1, bias1, bias1};
+#pragma unroll
+        for (int t = 0; t < 3; ++t)
+            z = __builtin_amdgcn_mfma_f32_16x16x4f32(4 * t + g < kIn ? xs[li][4 * t + g] : 0.0f, b1w[t], z, 0, 0, 0);
+        float g1[4], g2[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            g1[v] = gelu_d(z[v]);
+            h1[4 * g + v][j] = 4 * g + v < nr ? gelu_f(z[v]) : 0.0f;
+        }
+        __syncthreads();
+        z = f32x4{bias2, bias2, bias2, bias2};
+#pragma unroll
+        for (int t = 0; t < 16; ++t) z = __builtin_amdgcn_mfma_f32_16x16x4f32(h1[li][4 * t + g], b2w[t], z, 0, 0, 0);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            g2[v] = gelu_d(z[v]);
+            h2[4 * g + v][j] = 4 * g + v < nr ? gelu_f(z[v]) : 0.0f;
+        }
+        __syncthreads();
+        if (tid < 16) {
+            float d = 0.0f;
+            if (tid < nr) {
+                float zz = b3;
+#pragma unroll 16
+                for (int k = 0; k < kHid; ++k) zz += w3s[k] * h2[tid][k];
+                const float yy = y[s0 + tid];
+                const float wt = yy > 0.5f ? pos_weight : 1.0f;
+                const float ez = expf(-fabsf(zz));
+                const float sig = zz >= 0.0f ? 1.0f / (1.0f + ez) : ez / (1.0f + ez);
+                loss += double(wt) * (double(fmaxf(zz, 0.0f)) - double(zz) * yy + log1p(double(ez)));
+                d = wt * (sig - yy) / float(n);
+            }
+            dz[tid] = d;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int v = 0; v < 4; ++v)  // rows beyond the batch: zero, whatever the weights are
+            d2[4 * g + v][j] = 4 * g + v < nr ? dz[4 * g + v] * w3 * g2[v] : 0.0f;
+        __syncthreads();
+        z = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int t = 0; t < 16; ++t) z = __builtin_amdgcn_mfma_f32_16x16x4f32(d2[li][4 * t + g], b2t[t], z, 0, 0, 0);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) d1[4 * g + v][j] = 4 * g + v < nr ? z[v] * g1[v] : 0.0f;
+        // d1's columns of a wave are read by that wave only; the rows of the
+        // other arrays are complete since the last barrier
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const int r = 4 * t + g;
+            const double e2 = d2[r][j], e1 = d1[r][j];
+            a1 = __builtin_amdgcn_mfma_f64_16x16x4f64(e1, double(xs[r][li]), a1, 0, 0, 0);
+#pragma unroll
+            for (int nb = 0; nb < 4; ++nb)
+                a2[nb] = __builtin_amdgcn_mfma_f64_16x16x4f64(e2, double(h1[r][16 * nb + li]), a2[nb], 0, 0, 0);
+        }
+        if (tid < 64) {
+            for (int r = 0; r < 16; ++r) av += double(d2[r][tid]);
+        } else if (tid < 128) {
+            for (int r = 0; r < 16; ++r) av += double(dz[r]) * double(h2[r][tid - 64]);
+        } else if (tid == 128) {
+            for (int r = 0; r < 16; ++r) av += double(dz[r]);
+        }
+        __syncthreads();
+    }
+    double *out = part + int64_t(blockIdx.x) * kWeights;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const int row = 16 * wv + g + 4 * v;
+        if (li < kIn) out[kW1 + row * kIn + li] = a1[v];
+        else if (li == kIn) out[kB1 + row] = a1[v];
+#pragma unroll
+        for (int nb = 0; nb < 4; ++nb) out[kW2 + row * kHid + 16 * nb + li] = a2[nb][v];
+    }
+    if (tid < 64) out[kB2 + tid] = av;
+    else if (tid < 128) out[kW3 + tid - 64] = av;
+    else if (tid == 128) out[kB3] = av;
+    if (tid < 64) {
+        const double t = wave_sum(tid < 16 ? loss : 0.0);
+        if (tid == 0) loss_part[blockIdx.x] = t;
+    }
+}
+
+// gradient = sum of the blocks' sums in a fixed order (four interleaved
+// partial sums per weight, so that 64 weights a workgroup keep their loads
+// coalesced and four times the lanes busy), the mean loss, and the Adam update
+// of the weight where one is asked for
+__global__ __launch_bounds__(256) void k_train_reduce(const double *part, const double *loss_part, int nb, int64_t n,
+                                                      float *grad, double *loss, AdamArgs adam) {
+    __shared__ double red[4][64];
+    const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
+    const int i = int(blockIdx.x) * 64 + lane;
+    double s = 0.0;
+    if (i < kWeights) {
+#pragma unroll 8
+        for (int b = q; b < nb; b += 4) s += part[int64_t(b) * kWeights + i];
+    }
+    red[q][lane] = s;
+    if (blockIdx.x == 0 && q == 3) {
         double l = 0.0;
-        for (int b = 0; b < nlp; ++b) l += loss_part[b];
-        *loss = l / double(n);
+        for (int b = lane; b < nb; b += 64) l += loss_part[b];
+        l = wave_sum(l);
+        if (lane == 0) *loss = l / double(n);
     }
-    if (i >= kWeights) return;
-    int a, b;  // gradient = sum_s R[a] * R[b] (b < 0: sum_s R[a])
-    if (i < kB1) {
-        a = kRd1 + (i - kW1) / kIn;
-        b = kRx + (i - kW1) % kIn;
-    } else if (i < kW2) {
-        a = kRd1 + (i - kB1);
-        b = -1;
-    } else if (i < kB2) {
-        a = kRd2 + (i - kW2) / kHid;
-        b = kRh1 + (i - kW2) % kHid;
-    } else if (i < kW3) {
-        a = kRd2 + (i - kB2);
-        b = -1;
-    } else if (i < kB3) {
-        a = kRdz;
-        b = kRh2 + (i - kW3);
-    } else {
-        a = kRdz;
-        b = -1;
+    __syncthreads();
+    if (q == 0 && i < kWeights) {
+        const float gr = float((red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]));
+        grad[i] = gr;
+        if (adam.P) adam_one(adam, i, gr);
     }
-    double g = 0.0;
-    for (int64_t s = 0; s < n; ++s) {
-        const float *R = rec + s * kRec;
-        g += b < 0 ? double(R[a]) : double(R[a]) * double(R[b]);
-    }
-    grad[i] = float(g);
 }
 
-// Adam with bias correction; c1 = 1 - beta1^t, c2 = 1 - beta2^t
-__global__ __launch_bounds__(256) void k_adam(float *P, float *m, float *v, const float *grad, float lr, float c1,
-                                              float c2) {
+__global__ __launch_bounds__(256) void k_adam(AdamArgs a, const float *grad) {
     const int i = int(blockIdx.x) * 256 + threadIdx.x;
-    if (i >= kWeights) return;
-    const float g = grad[i];
-    const float mi = 0.9f * m[i] + 0.1f * g;
-    const float vi = 0.999f * v[i] + 0.001f * g * g;
-    m[i] = mi;
-    v[i] = vi;
-    P[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + 1e-8f);
+    if (i < kWeights) adam_one(a, i, grad[i]);
 }
 
 // standardisation statistics of a feature set (FP64, fixed order)

@@ -76,18 +76,18 @@ struct dvm_solver {
 };
 
 // The sensor network: host object over a caller-owned parameter block and
-// workspace (Adam moments, gradients, per-sample scratch).
+// workspace (Adam moments, gradients, per-block gradient sums).
 struct dvm_mlp {
     int64_t max_batch = 0;
     float *params = nullptr;
     char *ws = nullptr;
-    size_t off_m = 0, off_v = 0, off_grad = 0, off_rec = 0, off_lpart = 0, off_loss = 0, ws_bytes = 0;
+    size_t off_m = 0, off_v = 0, off_grad = 0, off_part = 0, off_lpart = 0, off_loss = 0, ws_bytes = 0;
     int64_t t = 0;  // Adam step count
 
     float *m() const { return reinterpret_cast<float *>(ws + off_m); }
     float *v() const { return reinterpret_cast<float *>(ws + off_v); }
     float *grad() const { return reinterpret_cast<float *>(ws + off_grad); }
-    float *rec() const { return reinterpret_cast<float *>(ws + off_rec); }
+    double *part() const { return reinterpret_cast<double *>(ws + off_part); }
     double *lpart() const { return reinterpret_cast<double *>(ws + off_lpart); }
     double *loss() const { return reinterpret_cast<double *>(ws + off_loss); }
 };
