@@ -171,6 +171,7 @@ struct LbmArgs {
     double relax;       // exp(-dt/tau) (exponential) or dt/tau (explicit Euler)
     int euler;
     int *flag;
+    int any_fine;       // the mesh has FINER faces
     int xcd_log2;       // workgroups of 256 cells go to the XCDs in runs of 2^xcd_log2
 };
 hipError_t launch_lbm_step(int q, bool fp64, const LbmArgs &a, hipStream_t st);
