@@ -454,7 +454,34 @@ __device__ __forceinline__ void add_moments(const Regs<F, NH, T> &fo, const VelG
     }
 }
 
+// Holds a value as computed here: without it the arithmetic of several axes is
+// sunk to where their sum is used, and every operand of it kept until then.
+__device__ __forceinline__ void pin(float &x) { asm volatile("" : "+v"(x)); }
+__device__ __forceinline__ void pin(double &x) { asm volatile("" : "+v"(x)); }
+
+__device__ __forceinline__ float fma_of(float x, float y, float z) { return __builtin_fmaf(x, y, z); }
+__device__ __forceinline__ double fma_of(double x, double y, double z) { return __builtin_fma(x, y, z); }
+
+struct NoTab {};
+// octants whose new values wait in LDS while the MUSCL step of a cell with level
+// jumps goes through the others: the 24^3 FP32 shape (three slots a thread, 72
+// registers for three workgroups a compute unit) would spill them
 template <typename F, int NH, int T>
+constexpr int muscl_park() {
+    return sizeof(F) == 4 && Lane<NH, T>::S >= 3 ? 3 : 0;
+}
+template <typename F, int N>
+struct Park {
+    F v[N];
+    __device__ __forceinline__ F *get() { return v; }
+};
+template <typename F>
+struct Park<F, 0> {
+    __device__ __forceinline__ F *get() { return nullptr; }
+};
+template <typename F>
+struct MusclTab;
+template <typename F, int NH, int T, bool MU = false>
 struct StepSmem {
     static constexpr int NW = (T + 63) / 64;
     double red[NW * 5];
@@ -463,6 +490,8 @@ struct StepSmem {
     // FP32: landing area of the FINER / WALL correction loads (per wave: 4
     // rows x S rounds x 64 lanes), filled by loads that write LDS directly
     float stage[std::is_same<F, float>::value ? NW : 1][std::is_same<F, float>::value ? 4 * Lane<NH, T>::S : 1][64];
+    std::conditional_t<MU, MusclTab<F>, NoTab> tab;
+    Park<F, MU ? muscl_park<F, NH, T>() * Lane<NH, T>::S * T : 0> park;
 };
 
 // Transport of the thread's slots; fo holds f on entry and f* on return.
@@ -597,7 +626,13 @@ __device__ __forceinline__ void transport(Regs<F, NH, T> &fo, const CellView &ce
 
 template <typename F>
 __device__ __forceinline__ F minmod(F l, F r) {
-    return l * r <= F(0) ? F(0) : (fabs(l) < fabs(r) ? l : r);
+    if constexpr (sizeof(F) == 4) {
+        // the median of 0 and the two, one instruction; a NaN on the right stays one
+        const float m = __builtin_amdgcn_fmed3f(0.0f, l, r);
+        return r != r ? r : m;
+    } else {
+        return l * r <= F(0) ? F(0) : (fabs(l) < fabs(r) ? l : r);
+    }
 }
 
 // A cell record read word by word through scalar loads (a neighbour's, used
@@ -627,83 +662,169 @@ __device__ __forceinline__ bool muscl_single_row(const DevCell *cells, int64_t c
     return ok;
 }
 
-// Value of cell x's face neighbour across face f for the thread's slots of
-// octant o (mean of the rows of a FINER face), and 1 / centre distance.
-// own: x's values (the OUTFLOW side).
-template <typename F, int NH, int T>
-__device__ __forceinline__ void muscl_side(const StepArgs &a, const RecRT &x, double h, int f, int o,
-                                           const F (&own)[Lane<NH, T>::S], F (&out)[Lane<NH, T>::S], F &inv) {
-    using L = Lane<NH, T>;
-    constexpr int S = L::S;
-    constexpr int64_t NV = 8 * L::B;
-    constexpr uint32_t kRow = uint32_t(NV * sizeof(F));
-    const F *fin = static_cast<const F *>(a.f_in);
-    const uint32_t voff = threadIdx.x * sizeof(F);
-    const int ty = x.type(f);
-    if (ty == DVM_FACE_SAME || ty == DVM_FACE_COARSER || ty == DVM_FACE_INFLOW) {
-        const Rsrc r = rsrc(ty == DVM_FACE_INFLOW ? static_cast<const F *>(a.ghost_in) : fin + int64_t(x.nbr(f, 0)) * NV,
-                            kRow);
-#pragma unroll
-        for (int q = 0; q < S; ++q) out[q] = bld<F>(r, voff, L::template soff<F>(o, q));
-        inv = F(1.0 / (ty == DVM_FACE_COARSER ? 1.5 * h : h));
-    } else if (ty == DVM_FACE_FINER) {
-        Rsrc r[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) r[k] = rsrc(fin + int64_t(x.nbr(f, k)) * NV, kRow);
-#pragma unroll
-        for (int q = 0; q < S; ++q) {
-            const uint32_t so = L::template soff<F>(o, q);
-            out[q] = F(0.25) * (((bld<F>(r[0], voff, so) + bld<F>(r[1], voff, so)) + bld<F>(r[2], voff, so)) +
-                                bld<F>(r[3], voff, so));
+// The stencil of a MUSCL cell, gathered once per cell into LDS: per face f the
+// row(s) across it, what lies behind each of the cells there (the far side) and
+// in front of a coarser one (its near side, four finer rows; everywhere else the
+// near side is the cell itself), as row addresses, with the limiter's factors.
+template <typename F>
+struct MusclTab {
+    uint64_t up[6][4];      // the row(s) across face f: four at a FINER face, else [0]
+    uint64_t far[6][4][4];  // behind up[f][k]: four rows or one
+    uint64_t near[6][4];    // bit kNear4: the four rows in front of up[f][0]
+    F iup[6];               // 1 / centre distance to the value across face f
+    F hu[6][4];             // half the width of cell up[f][k]; 0: it has no slope (touches a wall, or a ghost)
+    F ifar[6][4], inear[6]; // 1 / centre distances from up[f][k] to its far and near sides
+    uint32_t flag[6];
+};
+// What every octant needs of it (the first entries of each face), one word a
+// lane in two registers of every wave, so that the octant loop picks a face's
+// words by v_readlane instead of some 30 LDS reads an octant and wave.
+template <typename F>
+struct MusclWords {
+    static constexpr int W = sizeof(F) / 4, N = 5 + 2 * W;  // words of a factor; of a face's first group
+    uint32_t w0, w1;  // lane f * N + ..: up (2), far (2), flag, iup (W), hu (W); lane f * 2 W + ..: ifar (W), inear (W)
+    __device__ __forceinline__ explicit MusclWords(const MusclTab<F> &t) {
+        const int l = threadIdx.x & 63, f = min(l / N, 5), k = l % N;
+        const uint32_t *p = k < 2   ? reinterpret_cast<const uint32_t *>(&t.up[f][0]) + k
+                            : k < 4 ? reinterpret_cast<const uint32_t *>(&t.far[f][0][0]) + (k - 2)
+                            : k < 5 ? &t.flag[f]
+                            : k < 5 + W ? reinterpret_cast<const uint32_t *>(&t.iup[f]) + (k - 5)
+                                        : reinterpret_cast<const uint32_t *>(&t.hu[f][0]) + (k - 5 - W);
+        w0 = *p;
+        const int f1 = min(l / (2 * W), 5), k1 = l % (2 * W);
+        w1 = k1 < W ? reinterpret_cast<const uint32_t *>(&t.ifar[f1][0])[k1]
+                    : reinterpret_cast<const uint32_t *>(&t.inear[f1])[k1 - W];
+    }
+    static __device__ __forceinline__ uint32_t word(uint32_t w, int lane) {
+        return uint32_t(__builtin_amdgcn_readlane(int(w), lane));
+    }
+    static __device__ __forceinline__ F factor(uint32_t w, int lane) {
+        if constexpr (W == 1) return __builtin_bit_cast(float, word(w, lane));
+        else return __builtin_bit_cast(double, word(w, lane) | (uint64_t(word(w, lane + 1)) << 32));
+    }
+    __device__ __forceinline__ const void *row(int f, int at) const {
+        return reinterpret_cast<const void *>(word(w0, f * N + at) | (uint64_t(word(w0, f * N + at + 1)) << 32));
+    }
+    __device__ __forceinline__ const void *up(int f) const { return row(f, 0); }
+    __device__ __forceinline__ const void *far(int f) const { return row(f, 2); }
+    __device__ __forceinline__ uint32_t flag(int f) const { return word(w0, f * N + 4); }
+    __device__ __forceinline__ F iup(int f) const { return factor(w0, f * N + 5); }
+    __device__ __forceinline__ F hu(int f) const { return factor(w0, f * N + 5 + W); }
+    __device__ __forceinline__ F ifar(int f) const { return factor(w1, f * 2 * W); }
+    __device__ __forceinline__ F inear(int f) const { return factor(w1, f * 2 * W + W); }
+};
+constexpr uint32_t kUp4 = 1, kNear4 = 2;                // FINER face; COARSER face
+constexpr uint32_t kFar4 = 4;                           // << k: the far side of up[f][k] is four rows
+
+// Threads 0..23 (face f = t / 4, cell k = t % 4 across it) fill the table: the
+// records of all the neighbours are read side by side, two dependent trips to
+// memory per cell.  The caller synchronises.
+template <typename F, int64_t NV>
+__device__ __forceinline__ void muscl_table(MusclTab<F> &tab, const StepArgs &a, int64_t c) {
+    const int t = threadIdx.x;
+    if (t >= 24) return;
+    const int f = t >> 2, k = t & 3;
+    const DevCell &rec = a.cells[c];
+    const auto row = [&](int64_t i) {
+        return reinterpret_cast<uint64_t>(a.f_in) + uint64_t(i * NV * int64_t(sizeof(F)));
+    };
+    const auto inv = [](int ty, double h) {
+        return F(1.0 / (ty == DVM_FACE_COARSER ? 1.5 * h : ty == DVM_FACE_FINER ? 0.75 * h : h));
+    };
+    const int ty = rec.type[f];
+    const double h = a.h0 / double(1 << rec.level);
+    const bool finer = ty == DVM_FACE_FINER, inside = finer || ty == DVM_FACE_SAME || ty == DVM_FACE_COARSER;
+    if (!finer && k > 0) return;
+    const int64_t x = inside ? rec.nbr[f][k] : c;
+    tab.up[f][k] = ty == DVM_FACE_INFLOW ? reinterpret_cast<uint64_t>(a.ghost_in)
+                   : ty == DVM_FACE_WALL ? reinterpret_cast<uint64_t>(a.wall_m1)
+                                         : row(x);  // OUTFLOW: zero gradient, the cell itself
+    if (k == 0) tab.iup[f] = inv(ty, h);
+    uint32_t flag = finer ? kUp4 : ty == DVM_FACE_COARSER ? kNear4 : 0;
+    if (!inside) {
+        tab.far[f][0][0] = tab.up[f][0];
+        tab.hu[f][0] = F(0);
+        tab.ifar[f][0] = tab.inear[f] = F(1.0 / h);
+    } else {
+        const DevCell &u = a.cells[x];
+        const int tf = u.type[f];
+        const double hx = a.h0 / double(1 << u.level);
+        if (tf == DVM_FACE_FINER) {
+            flag |= kFar4 << k;
+            for (int j = 0; j < 4; ++j) tab.far[f][k][j] = row(u.nbr[f][j]);
+        } else {
+            tab.far[f][k][0] = tf == DVM_FACE_SAME || tf == DVM_FACE_COARSER ? row(u.nbr[f][0])
+                               : tf == DVM_FACE_INFLOW ? reinterpret_cast<uint64_t>(a.ghost_in)
+                                                       : row(x);  // OUTFLOW, WALL: its own value
         }
-        inv = F(1.0 / (0.75 * h));
-    } else {  // OUTFLOW (WALL: the slope is zero anyway)
-#pragma unroll
-        for (int q = 0; q < S; ++q) out[q] = own[q];
-        inv = F(1.0 / h);
+        tab.ifar[f][k] = inv(tf, hx);
+        tab.hu[f][k] = (u.flags & 1) ? F(0) : F(0.5 * hx);
+        if (k == 0) {
+            tab.inear[f] = inv(u.type[f ^ 1], hx);
+            if (ty == DVM_FACE_COARSER)
+                for (int j = 0; j < 4; ++j) tab.near[f][j] = row(u.nbr[f ^ 1][j]);
+        }
     }
+    // the four lanes of a FINER face (consecutive, all here) put their bits together
+    if (finer) {
+        flag |= __builtin_amdgcn_mov_dpp(int(flag), 0xb1, 0xf, 0xf, true);
+        flag |= __builtin_amdgcn_mov_dpp(int(flag), 0x4e, 0xf, 0xf, true);
+    }
+    if (k == 0) tab.flag[f] = flag;
 }
 
-// D of cell x on axis b for the thread's slots of octant o, the velocity
-// component's sign bit sb (1: positive, the value at x's high face).
-template <typename F, int NH, int T>
-__device__ __forceinline__ void muscl_face_value(const StepArgs &a, int64_t x, int b, int sb, int o,
-                                                 F (&out)[Lane<NH, T>::S]) {
-    using L = Lane<NH, T>;
-    constexpr int S = L::S;
-    constexpr int64_t NV = 8 * L::B;
-    const F *fin = static_cast<const F *>(a.f_in);
-    const uint32_t voff = threadIdx.x * sizeof(F);
-    const RecRT r(a.cells, x);
-    const Rsrc row = rsrc(fin + x * NV, uint32_t(NV * sizeof(F)));
-    F fx[S];
+// Four rows of octant offset so for the thread's slots, all loads in flight at
+// once: FP32 straight into this wave's part of LDS (no registers held), FP64 in
+// registers.  get(k, q) is row k's value of slot q; done() before the next use.
+template <typename F, int S>
+struct FourRows {
+    F x[sizeof(F) == 4 ? 1 : 4][sizeof(F) == 4 ? 1 : S];
+    float *wst;
+    __device__ __forceinline__ void load(const uint64_t (&at)[4], uint32_t bytes, uint32_t voff, uint32_t so, uint32_t round,
+                                         float *stage) {
+        if constexpr (sizeof(F) == 4) {
+            wst = stage + (threadIdx.x >> 6) * (4 * S * 64);
 #pragma unroll
-    for (int q = 0; q < S; ++q) fx[q] = bld<F>(row, voff, L::template soff<F>(o, q));
-    if (r.flags() & 1) {
+            for (int k = 0; k < 4; ++k) {
+                const Rsrc r = rsrc(reinterpret_cast<const void *>(at[k]), bytes);
 #pragma unroll
-        for (int q = 0; q < S; ++q) out[q] = fx[q];
-        return;
+                for (int q = 0; q < S; ++q)
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                        r, (__attribute__((address_space(3))) void *)(wst + (q * 4 + k) * 64), 4, voff, so + q * round, 0, 0);
+            }
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        } else {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const Rsrc r = rsrc(reinterpret_cast<const void *>(at[k]), bytes);
+#pragma unroll
+                for (int q = 0; q < S; ++q) x[k][q] = bld<F>(r, voff, so + q * round);
+            }
+        }
     }
-    const double h = a.h0 / double(1 << r.level());
-    F lo[S], hi[S], ilo, ihi;
-    muscl_side<F, NH, T>(a, r, h, 2 * b, o, fx, lo, ilo);
-    muscl_side<F, NH, T>(a, r, h, 2 * b + 1, o, fx, hi, ihi);
-    const F half = F(sb ? 0.5 * h : -0.5 * h);
+    __device__ __forceinline__ F get(int k, int q) const {
+        if constexpr (sizeof(F) == 4) return wst[(q * 4 + k) * 64 + (threadIdx.x & 63)];
+        else return x[k][q];
+    }
+    __device__ __forceinline__ void mean(F (&out)[S]) const {
 #pragma unroll
-    for (int q = 0; q < S; ++q) out[q] = fx[q] + half * minmod((fx[q] - lo[q]) * ilo, (hi[q] - fx[q]) * ihi);
-}
+        for (int q = 0; q < S; ++q) out[q] = F(0.25) * (((get(0, q) + get(1, q)) + get(2, q)) + get(3, q));
+        done();
+    }
+    __device__ __forceinline__ void done() const {
+        // read before the next loads overwrite the slots
+        if constexpr (sizeof(F) == 4) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    }
+};
 
-// MUSCL transport of the thread's slots; fo holds f on entry (FAST with
-// LATE_OWN: loaded here, octant by octant) and f* on return.
-//   FAST: the cells of muscl_single_row: per face the neighbour row and the
-//         row behind the neighbour, selected once per cell; the loads of an
-//         octant are independent of each other and issued together;
-//         WALLS: such a cell with a diffuse-wall face (no slope of its own;
-//         through a wall face enters rho_w times the wall Maxwellian), whose
-//         wall densities are in rho_w;
-//   else: any cell (level jumps on either hop, walls): the stencil is read
-//         from the neighbours' records, axis by axis.
-template <typename F, int NH, int T, bool FAST, bool LATE_OWN, bool WALLS = false>
+// MUSCL transport of the cells of muscl_single_row; fo holds f* on return (and
+// f on entry where WALLS; else it is loaded here, octant by octant).  Per face
+// the neighbour row and the row behind the neighbour, selected once per cell;
+// the loads of an octant are independent of each other and issued together.
+// WALLS: a cell with a diffuse-wall face (no slope of its own; through a wall
+// face enters rho_w times the wall Maxwellian), whose wall densities are in
+// rho_w.
+template <typename F, int NH, int T, bool WALLS>
 __device__ __forceinline__ void transport_muscl(Regs<F, NH, T> &fo, const CellView &cell, int64_t c,
                                                 const Rsrc &own, const StepArgs &a, const double *rho_w, double dth,
                                                 double (&m)[5]) {
@@ -716,109 +837,69 @@ __device__ __forceinline__ void transport_muscl(Regs<F, NH, T> &fo, const CellVi
     const F *fin = static_cast<const F *>(a.f_in);
     const double h = a.h0 / double(1 << cell.level());
     const F hh = F(0.5 * h), ih = F(1.0 / h);
-    if constexpr (FAST) {
-        // per face f: the cell whose row lies across f (the inflow ghost: -1;
-        // the wall Maxwellian: -2; an OUTFLOW face: the cell itself) and,
-        // behind a SAME neighbour u,
-        // the next one along the axis (u itself at an OUTFLOW or WALL face);
-        // 1/distance from u to that one; whether u has a slope (SAME and not
-        // touching a wall)
-        int32_t Ni[6], Fi[6];
-        uint32_t on = 0, farc = 0;
+    // per face f: the cell whose row lies across f (the inflow ghost: -1;
+    // the wall Maxwellian: -2; an OUTFLOW face: the cell itself) and,
+    // behind a SAME neighbour u,
+    // the next one along the axis (u itself at an OUTFLOW or WALL face);
+    // 1/distance from u to that one; whether u has a slope (SAME and not
+    // touching a wall)
+    int32_t Ni[6], Fi[6];
+    uint32_t on = 0, farc = 0;
 #pragma unroll
-        for (int f = 0; f < 6; ++f) {
-            const int ty = cell.type(f);
-            Ni[f] = ty == DVM_FACE_SAME     ? cell.nbr(f, 0)
-                    : ty == DVM_FACE_INFLOW ? -1
-                    : ty == DVM_FACE_WALL   ? -2
-                                            : int32_t(c);
-            Fi[f] = Ni[f];
-            if (ty == DVM_FACE_SAME) {
-                const RecRT u(a.cells, Ni[f]);
-                const int tu = u.type(f);
-                if (tu == DVM_FACE_SAME || tu == DVM_FACE_COARSER) Fi[f] = u.nbr(f, 0);
-                else if (tu == DVM_FACE_INFLOW) Fi[f] = -1;
-                on |= uint32_t(!(u.flags() & 1)) << f;
-                farc |= uint32_t(tu == DVM_FACE_COARSER) << f;
-            }
+    for (int f = 0; f < 6; ++f) {
+        const int ty = cell.type(f);
+        Ni[f] = ty == DVM_FACE_SAME     ? cell.nbr(f, 0)
+                : ty == DVM_FACE_INFLOW ? -1
+                : ty == DVM_FACE_WALL   ? -2
+                                        : int32_t(c);
+        Fi[f] = Ni[f];
+        if (ty == DVM_FACE_SAME) {
+            const RecRT u(a.cells, Ni[f]);
+            const int tu = u.type(f);
+            if (tu == DVM_FACE_SAME || tu == DVM_FACE_COARSER) Fi[f] = u.nbr(f, 0);
+            else if (tu == DVM_FACE_INFLOW) Fi[f] = -1;
+            on |= uint32_t(!(u.flags() & 1)) << f;
+            farc |= uint32_t(tu == DVM_FACE_COARSER) << f;
         }
-        // descriptors and per-face factors made once, before the octant loop
-        // and without branches: a select inside the loop becomes a branch,
-        // and the compiler then hoists every octant's loads and spills them
-        const uint64_t ghost = reinterpret_cast<uint64_t>(a.ghost_in), base = reinterpret_cast<uint64_t>(fin);
-        const uint64_t wallm = reinterpret_cast<uint64_t>(a.wall_m1);
-        const auto row = [&](int32_t i) {
-            const uint64_t at = base + uint64_t(int64_t(i < 0 ? 0 : i) * NV * int64_t(sizeof(F)));
-            return rsrc(reinterpret_cast<const void *>(i < 0 ? (i == -1 ? ghost : wallm) : at), kRow);
-        };
-        const F i15 = F(1.0 / (1.5 * h));
-        Rsrc RN[6], RF[6];
-        F ifar[6], son[6];
+    }
+    // descriptors and per-face factors made once, before the octant loop
+    // and without branches: a select inside the loop becomes a branch,
+    // and the compiler then hoists every octant's loads and spills them
+    const uint64_t ghost = reinterpret_cast<uint64_t>(a.ghost_in), base = reinterpret_cast<uint64_t>(fin);
+    const uint64_t wallm = reinterpret_cast<uint64_t>(a.wall_m1);
+    const auto row = [&](int32_t i) {
+        const uint64_t at = base + uint64_t(int64_t(i < 0 ? 0 : i) * NV * int64_t(sizeof(F)));
+        return rsrc(reinterpret_cast<const void *>(i < 0 ? (i == -1 ? ghost : wallm) : at), kRow);
+    };
+    const F i15 = F(1.0 / (1.5 * h));
+    Rsrc RN[6], RF[6];
+    F ifar[6], son[6];
 #pragma unroll
-        for (int f = 0; f < 6; ++f) {
-            RN[f] = row(Ni[f]);
-            RF[f] = row(Fi[f]);
-            ifar[f] = (farc >> f) & 1u ? i15 : ih;
-            son[f] = (on >> f) & 1u ? F(1) : F(0);
-        }
-        if constexpr (WALLS) {
-#pragma unroll
-            for (int o = 0; o < 8; ++o) {
-                const int sg[3] = {o >> 2, (o >> 1) & 1, o & 1};
-                // rho_w on a wall face, 1 on the others (an exact product);
-                // read per octant, after the fence, to keep them out of the
-                // registers the loads need
-                F sN[3];
-#pragma unroll
-                for (int b = 0; b < 3; ++b) sN[b] = uniform_value(F(rho_w[sg[b] ? 2 * b : 2 * b + 1]));
-                F up[3][S], far[3][S];
-#pragma unroll
-                for (int q = 0; q < S; ++q) {
-                    const uint32_t so = L::template soff<F>(o, q);
-#pragma unroll
-                    for (int b = 0; b < 3; ++b) {
-                        const int fu = sg[b] ? 2 * b : 2 * b + 1;
-                        up[b][q] = bld<F>(RN[fu], voff, so);
-                        far[b][q] = bld<F>(RF[fu], voff, so);
-                    }
-                }
-#pragma unroll
-                for (int q = 0; q < S; ++q) {
-                    int a3[3];
-                    ln.axes_late(q, a3[0], a3[1], a3[2]);
-                    const F v = fo[o][q];
-                    F t = F(0);
-#pragma unroll
-                    for (int b = 0; b < 3; ++b) {
-                        const int fu = sg[b] ? 2 * b : 2 * b + 1;
-                        const F half = sg[b] ? hh : -hh;
-                        // son is 0 on a wall face: there the slope drops out
-                        // and din is rho_w times the wall row
-                        const F u = up[b][q];
-                        const F su = sg[b] ? minmod((u - far[b][q]) * ifar[fu], (v - u) * ih)
-                                           : minmod((u - v) * ih, (far[b][q] - u) * ifar[fu]);
-                        const F din = sN[b] * u + half * (son[fu] * su);
-                        const F nub = F(dth) * (F(a3[b]) + F(0.5)) * F(a.g.dv[b]);
-                        t += nub * (v - din);  // a wall cell has no slope of its own
-                    }
-                    fo[o][q] = v - t;
-                }
-                asm volatile("" ::: "memory");  // one octant's loads in flight at a time
-            }
-        } else {
+    for (int f = 0; f < 6; ++f) {
+        RN[f] = row(Ni[f]);
+        RF[f] = row(Fi[f]);
+        ifar[f] = (farc >> f) & 1u ? i15 : ih;
+        son[f] = (on >> f) & 1u ? F(1) : F(0);
+    }
+    if constexpr (WALLS) {
 #pragma unroll
         for (int o = 0; o < 8; ++o) {
             const int sg[3] = {o >> 2, (o >> 1) & 1, o & 1};
-            F lo[3][S], hi[3][S], far[3][S];
+            // rho_w on a wall face, 1 on the others (an exact product);
+            // read per octant, after the fence, to keep them out of the
+            // registers the loads need
+            F sN[3];
+#pragma unroll
+            for (int b = 0; b < 3; ++b) sN[b] = uniform_value(F(rho_w[sg[b] ? 2 * b : 2 * b + 1]));
+            F up[3][S], far[3][S];
 #pragma unroll
             for (int q = 0; q < S; ++q) {
                 const uint32_t so = L::template soff<F>(o, q);
-                if constexpr (LATE_OWN) fo[o][q] = bld<F>(own, voff, so);
 #pragma unroll
                 for (int b = 0; b < 3; ++b) {
-                    lo[b][q] = bld<F>(RN[2 * b], voff, so);
-                    hi[b][q] = bld<F>(RN[2 * b + 1], voff, so);
-                    far[b][q] = bld<F>(RF[sg[b] ? 2 * b : 2 * b + 1], voff, so);  // a positive component enters through the low face
+                    const int fu = sg[b] ? 2 * b : 2 * b + 1;
+                    up[b][q] = bld<F>(RN[fu], voff, so);
+                    far[b][q] = bld<F>(RF[fu], voff, so);
                 }
             }
 #pragma unroll
@@ -831,93 +912,242 @@ __device__ __forceinline__ void transport_muscl(Regs<F, NH, T> &fo, const CellVi
                 for (int b = 0; b < 3; ++b) {
                     const int fu = sg[b] ? 2 * b : 2 * b + 1;
                     const F half = sg[b] ? hh : -hh;
-                    const F dc = v + half * minmod((v - lo[b][q]) * ih, (hi[b][q] - v) * ih);
-                    const F up = sg[b] ? lo[b][q] : hi[b][q];
-                    const F su = sg[b] ? minmod((up - far[b][q]) * ifar[fu], (v - up) * ih)
-                                       : minmod((up - v) * ih, (far[b][q] - up) * ifar[fu]);
-                    const F din = up + half * (son[fu] * su);
+                    // son is 0 on a wall face: there the slope drops out
+                    // and din is rho_w times the wall row
+                    const F u = up[b][q];
+                    const F su = sg[b] ? minmod((u - far[b][q]) * ifar[fu], (v - u) * ih)
+                                       : minmod((u - v) * ih, (far[b][q] - u) * ifar[fu]);
+                    const F din = sN[b] * u + half * (son[fu] * su);
                     const F nub = F(dth) * (F(a3[b]) + F(0.5)) * F(a.g.dv[b]);
-                    t += nub * (dc - din);
+                    t += nub * (v - din);  // a wall cell has no slope of its own
                 }
                 fo[o][q] = v - t;
             }
             asm volatile("" ::: "memory");  // one octant's loads in flight at a time
         }
-        }
     } else {
-        // runtime loops over octants and axes (one copy of the code); the
-        // register arrays are reached through uniform selects, never indexed
-        const RecRT rc(a.cells, c);
-        const bool wall = cell.flags() & 1;
+#pragma unroll
+    for (int o = 0; o < 8; ++o) {
+        const int sg[3] = {o >> 2, (o >> 1) & 1, o & 1};
+        F lo[3][S], hi[3][S], far[3][S];
+#pragma unroll
+        for (int q = 0; q < S; ++q) {
+            const uint32_t so = L::template soff<F>(o, q);
+            fo[o][q] = bld<F>(own, voff, so);
+#pragma unroll
+            for (int b = 0; b < 3; ++b) {
+                lo[b][q] = bld<F>(RN[2 * b], voff, so);
+                hi[b][q] = bld<F>(RN[2 * b + 1], voff, so);
+                far[b][q] = bld<F>(RF[sg[b] ? 2 * b : 2 * b + 1], voff, so);  // a positive component enters through the low face
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < S; ++q) {
+            int a3[3];
+            ln.axes_late(q, a3[0], a3[1], a3[2]);
+            const F v = fo[o][q];
+            F t = F(0);
+#pragma unroll
+            for (int b = 0; b < 3; ++b) {
+                const int fu = sg[b] ? 2 * b : 2 * b + 1;
+                const F half = sg[b] ? hh : -hh;
+                const F dc = v + half * minmod((v - lo[b][q]) * ih, (hi[b][q] - v) * ih);
+                const F up = sg[b] ? lo[b][q] : hi[b][q];
+                const F su = sg[b] ? minmod((up - far[b][q]) * ifar[fu], (v - up) * ih)
+                                   : minmod((up - v) * ih, (far[b][q] - up) * ifar[fu]);
+                const F din = up + half * (son[fu] * su);
+                const F nub = F(dth) * (F(a3[b]) + F(0.5)) * F(a.g.dv[b]);
+                t += nub * (dc - din);
+            }
+            fo[o][q] = v - t;
+        }
+        asm volatile("" ::: "memory");  // one octant's loads in flight at a time
+    }
+    }
+    add_moments<F, NH, T>(fo, a.g, m);
+}
+
+// MUSCL transport of any other cell (level jumps on either hop, with or without
+// walls); fo holds f* on return.  Octant by octant (a loop that is not unrolled;
+// the first octants' results wait in LDS, see muscl_park): the own value and the
+// upwind row, the downwind row and the row behind the upwind cell of two axes
+// are in flight together, the third axis' follow into the first one's registers
+// (all three at once spill), and what a level jump needs besides is loaded four
+// rows at a time.  With a = (v - up) / d_up and b = (dn - v) / d_dn the face
+// value f + sgn(xi) (h/2) minmod(lo, hi) is v + (h/2) minmod(a, b) for either
+// sign of xi, bit for bit, so the code does not depend on the octant.
+// What bounds it: the latency of these trips, some 20 a cell, at 27 waves a
+// compute unit.  Walking the neighbours' records per octant and axis instead
+// cost 24 chains of dependent scalar loads a cell, paid by every cell with a
+// level jump within two hops (31 % to 95 % of the cells of these meshes):
+//   Mach-2 sphere (58,768 cells, 24^3, FP32)      5.80 -> 4.38 ms
+//   octree, 40 % refined (30,400 cells, 24^3)     5.76 -> 3.56 ms
+//   the same in FP64 (10,427 cells)               3.40 -> 2.13 ms
+// (with them the median instruction in minmod, 8 % where no cell has a jump).
+// Measured and not kept: the same code for every cell at 576 and at 896 threads
+// (no jumps: 2.7 ms against 1.6), the axes one at a time with the next one
+// prefetched (5.0 ms on the octree), two launches, one per kind of cell (3.7
+// and 5.0 ms).
+template <typename F, int NH, int T>
+__device__ __forceinline__ void transport_muscl_jumps(Regs<F, NH, T> &fo, const CellView &cell, const Rsrc &own,
+                                                      const StepArgs &a, const MusclTab<F> &tab, const double *rho_w,
+                                                      double dth, double (&m)[5], float *stage, F *park) {
+    using L = Lane<NH, T>;
+    constexpr int S = L::S;
+    constexpr int kPark = muscl_park<F, NH, T>();
+    constexpr uint32_t kRow = uint32_t(8 * L::B * sizeof(F)), kRound = uint32_t(T * sizeof(F));
+    const L ln;
+    const uint32_t voff = threadIdx.x * sizeof(F);
+    const bool walled = cell.flags() & 1;
+    const double h = a.h0 / double(1 << cell.level());
+    const F hh = walled ? F(0) : F(0.5 * h);  // a cell that touches a wall has no slope
+    const MusclWords<F> words(tab);
+    // dt/h |xi_b| of the thread's slots (of every slot along the axes that do not
+    // change from round to round)
+    F nu[3][S];
+#pragma unroll
+    for (int q = 0; q < S; ++q) {
+        int a3[3];
+        ln.axes(q, a3[0], a3[1], a3[2]);
+#pragma unroll
+        for (int b = 0; b < 3; ++b) {
+            nu[b][q] = L::kQInv && b > 0 && q > 0 ? nu[b][0] : F(dth) * (F(a3[b]) + F(0.5)) * F(a.g.dv[b]);
+            if (!(L::kQInv && b > 0 && q > 0)) pin(nu[b][q]);
+        }
+    }
 #pragma nounroll
-        for (int o = 0; o < 8; ++o) {
-            F v[S], t[S];
+    for (int o = 0; o < 8; ++o) {
+        const uint32_t so = uint32_t(o) * uint32_t(L::B * sizeof(F));
+        int fu[3];
+        uint32_t fl[3];  // kUp4 | kNear4 | kFar4.. of the upwind face; kDn4: FINER downwind
+        constexpr uint32_t kDn4 = 1u << 8;
+        F v[S], up[2][S], dn[2][S], fr[2][S];  // two axes' rows in flight at a time
+#pragma unroll
+        for (int q = 0; q < S; ++q) v[q] = bld<F>(own, voff, so + q * kRound);
+        const auto fetch = [&](int b) {
+            const int x = b & 1;
+            fu[b] = 2 * b + 1 - ((o >> (2 - b)) & 1);  // a positive component enters through the low face
+            const int fd = fu[b] ^ 1;
+            fl[b] = words.flag(fu[b]) | ((words.flag(fd) & kUp4) << 8);
+            // values made of several rows are read further down: nothing here
+            const Rsrc ru = rsrc(words.up(fu[b]), fl[b] & kUp4 ? 0 : kRow);
+            const Rsrc rd = rsrc(words.up(fd), fl[b] & kDn4 ? 0 : kRow);
+            const Rsrc rf = rsrc(words.far(fu[b]), fl[b] & (kUp4 | kFar4) ? 0 : kRow);
 #pragma unroll
             for (int q = 0; q < S; ++q) {
-                v[q] = fo[0][q];
-#pragma unroll
-                for (int k = 1; k < 8; ++k) v[q] = o == k ? fo[k][q] : v[q];
-                t[q] = F(0);
+                up[x][q] = bld<F>(ru, voff, so + q * kRound);
+                dn[x][q] = bld<F>(rd, voff, so + q * kRound);
+                fr[x][q] = bld<F>(rf, voff, so + q * kRound);
             }
-#pragma nounroll
-            for (int b = 0; b < 3; ++b) {
-                const int sb = (o >> (2 - b)) & 1;
-                const F half = sb ? hh : -hh;
-                F dc[S], in[S];
-                if (wall) {
+        };
+        fetch(0);
+        fetch(1);
+        F t[S];
 #pragma unroll
-                    for (int q = 0; q < S; ++q) dc[q] = v[q];
-                } else {
-                    F lo[S], hi[S], ilo, ihi;
-                    muscl_side<F, NH, T>(a, rc, h, 2 * b, o, v, lo, ilo);
-                    muscl_side<F, NH, T>(a, rc, h, 2 * b + 1, o, v, hi, ihi);
+        for (int q = 0; q < S; ++q) t[q] = F(0);
 #pragma unroll
-                    for (int q = 0; q < S; ++q) dc[q] = v[q] + half * minmod((v[q] - lo[q]) * ilo, (hi[q] - v[q]) * ihi);
+        for (int b = 0; b < 3; ++b) {
+            const int f = fu[b];
+            F din[S];
+            FourRows<F, S> four;
+            if (fl[b] & kDn4) {
+                four.load(tab.up[f ^ 1], kRow, voff, so, kRound, stage);
+                four.mean(dn[b & 1]);
+            }
+            const F inr = words.inear(f);
+            if (!(fl[b] & kUp4)) {
+                if (fl[b] & kFar4) {
+                    four.load(tab.far[f][0], kRow, voff, so, kRound, stage);
+                    four.mean(fr[b & 1]);
                 }
-                const int fu = sb ? 2 * b : 2 * b + 1;  // a positive component enters through the low face
-                const int ty = rc.type(fu);
-                if (ty == DVM_FACE_SAME || ty == DVM_FACE_COARSER || ty == DVM_FACE_FINER) {
-                    // one upwind cell, or four behind sub-faces of a quarter of the area each
-                    const int nk = ty == DVM_FACE_FINER ? 4 : 1;
+                const F hu = words.hu(f), ifr = words.ifar(f);
+                if (fl[b] & kNear4) {
+                    four.load(tab.near[f], kRow, voff, so, kRound, stage);
+                    four.mean(din);
+#pragma unroll
+                    for (int q = 0; q < S; ++q)
+                        din[q] = minmod((up[b & 1][q] - fr[b & 1][q]) * ifr, (din[q] - up[b & 1][q]) * inr);
+                } else {
+#pragma unroll
+                    for (int q = 0; q < S; ++q)
+                        din[q] = minmod((up[b & 1][q] - fr[b & 1][q]) * ifr, (v[q] - up[b & 1][q]) * inr);
+                }
+                if (walled) {
+                    // rho_w times the wall Maxwellian enters through a wall face (1 on the others)
+                    const F sN = uniform_value(F(rho_w[f]));
+#pragma unroll
+                    for (int q = 0; q < S; ++q) din[q] = fma_of(hu, din[q], sN * up[b & 1][q]);
+                } else {
+#pragma unroll
+                    for (int q = 0; q < S; ++q) din[q] = up[b & 1][q] + hu * din[q];
+                }
+            } else {
+                // four finer upwind cells behind sub-faces of a quarter of the area
+                // each; up becomes their mean
+                const auto one = [&](int k, int q, F u, F fk, F hu, F ifr) {
+                    const F d = u + hu * minmod((u - fk) * ifr, (v[q] - u) * inr);
+                    up[b & 1][q] = k == 0 ? u : up[b & 1][q] + u;
+                    din[q] = k == 0 ? d : din[q] + d;
+                };
 #pragma nounroll
-                    for (int k = 0; k < nk; ++k) {
-                        F x[S];
-                        muscl_face_value<F, NH, T>(a, rc.nbr(fu, k), b, sb, o, x);
+                for (int k = 0; k < 4; k += 2) {
+                    if (fl[b] & ((kFar4 << k) | (kFar4 << (k + 1)))) {
+#pragma nounroll
+                        for (int e = k; e < k + 2; ++e) {
+                            const Rsrc ru = rsrc(reinterpret_cast<const void *>(tab.up[f][e]), kRow);
+                            const Rsrc rf = rsrc(reinterpret_cast<const void *>(tab.far[f][e][0]), kRow);
+                            const F hu = uniform_value(tab.hu[f][e]), ifr = uniform_value(tab.ifar[f][e]);
+                            if (fl[b] & (kFar4 << e)) {
+                                four.load(tab.far[f][e], kRow, voff, so, kRound, stage);
+                                four.mean(fr[b & 1]);
+                            } else {
 #pragma unroll
-                        for (int q = 0; q < S; ++q) in[q] = k == 0 ? x[q] : in[q] + x[q];
+                                for (int q = 0; q < S; ++q) fr[b & 1][q] = bld<F>(rf, voff, so + q * kRound);
+                            }
+#pragma unroll
+                            for (int q = 0; q < S; ++q) one(e, q, bld<F>(ru, voff, so + q * kRound), fr[b & 1][q], hu, ifr);
+                        }
+                    } else {
+                        const uint64_t at[4] = {tab.up[f][k], tab.far[f][k][0], tab.up[f][k + 1], tab.far[f][k + 1][0]};
+                        four.load(at, kRow, voff, so, kRound, stage);
+                        const F h0 = uniform_value(tab.hu[f][k]), i0 = uniform_value(tab.ifar[f][k]);
+                        const F h1 = uniform_value(tab.hu[f][k + 1]), i1 = uniform_value(tab.ifar[f][k + 1]);
+#pragma unroll
+                        for (int q = 0; q < S; ++q) {
+                            one(k, q, four.get(0, q), four.get(1, q), h0, i0);
+                            one(k + 1, q, four.get(2, q), four.get(3, q), h1, i1);
+                        }
+                        four.done();
                     }
-                    if (nk == 4) {
-#pragma unroll
-                        for (int q = 0; q < S; ++q) in[q] *= F(0.25);
-                    }
-                } else if (ty == DVM_FACE_INFLOW || ty == DVM_FACE_WALL) {
-                    const bool inflow = ty == DVM_FACE_INFLOW;
-                    const Rsrc r = rsrc(inflow ? a.ghost_in : a.wall_m1, kRow);
-                    const F sc = inflow ? F(1) : F(rho_w[fu]);
-#pragma unroll
-                    for (int q = 0; q < S; ++q) in[q] = sc * bld<F>(r, voff, L::template soff<F>(o, q));
-                } else {  // OUTFLOW: zero gradient
-#pragma unroll
-                    for (int q = 0; q < S; ++q) in[q] = v[q];
                 }
 #pragma unroll
                 for (int q = 0; q < S; ++q) {
-                    int a3[3];
-                    ln.axes_late(q, a3[0], a3[1], a3[2]);
-                    const int ab = b == 0 ? a3[0] : b == 1 ? a3[1] : a3[2];
-                    const double dvb = b == 0 ? a.g.dv[0] : b == 1 ? a.g.dv[1] : a.g.dv[2];
-                    const F nub = F(dth) * (F(ab) + F(0.5)) * F(dvb);
-                    t[q] += nub * (dc[q] - in[q]);
+                    up[b & 1][q] *= F(0.25);
+                    din[q] *= F(0.25);
                 }
             }
+            const F iu = words.iup(f), id = words.iup(f ^ 1);
 #pragma unroll
             for (int q = 0; q < S; ++q) {
-                const F r = v[q] - t[q];
-#pragma unroll
-                for (int k = 0; k < 8; ++k) fo[k][q] = o == k ? r : fo[k][q];
+                const F dc = v[q] + hh * minmod((v[q] - up[b & 1][q]) * iu, (dn[b & 1][q] - v[q]) * id);
+                t[q] += nu[b][q] * (dc - din[q]);
+                pin(t[q]);
             }
+            asm volatile("" ::: "memory");
+            if (b == 0) fetch(2);  // into the registers of the first
         }
+#pragma unroll
+        for (int q = 0; q < S; ++q) {
+#pragma unroll
+            for (int k = kPark; k < 8; ++k) fo[k][q] = o == k ? v[q] - t[q] : fo[k][q];
+            if (o < kPark) park[(o * S + q) * T + threadIdx.x] = v[q] - t[q];
+        }
+        asm volatile("" ::: "memory");  // one octant's loads in flight at a time
     }
+#pragma unroll
+    for (int k = 0; k < kPark; ++k)
+#pragma unroll
+        for (int q = 0; q < S; ++q) fo[k][q] = park[(k * S + q) * T + threadIdx.x];
     add_moments<F, NH, T>(fo, a.g, m);
 }
 
@@ -932,7 +1162,7 @@ struct NoHook {
 // One fused step of cell c by the calling workgroup.
 // MU: 0 first order, 1 MUSCL (any cell), 2 MUSCL (a cell of muscl_single_row).
 template <typename F, int NH, int T, int FENCE, bool NT, int MU, bool REG = false, class Hook = NoHook>
-__device__ __forceinline__ void step_cell(const StepArgs &a, int64_t c, StepSmem<F, NH, T> &sm,
+__device__ __forceinline__ void step_cell(const StepArgs &a, int64_t c, StepSmem<F, NH, T, (MU != 0)> &sm,
                                           const Hook &hook = Hook()) {
     constexpr int B = NH * NH * NH;
     constexpr int64_t NV = 8 * B;
@@ -957,16 +1187,19 @@ __device__ __forceinline__ void step_cell(const StepArgs &a, int64_t c, StepSmem
     constexpr bool kLateOwn = REG && std::is_same<Hook, NoHook>::value;
     F fo[8][S];
     const uint32_t voff = tid * sizeof(F);
-    if constexpr (!kLateOwn) {
+    if constexpr (MU == 1) muscl_table<F, NV>(sm.tab, a, c);
+    // (the MUSCL step of any cell loads its values octant by octant too; whole
+    // first only where there are wall densities to sum)
+    if (MU == 1 ? (cell.flags() & 1) != 0 : !kLateOwn) {
 #pragma unroll
         for (int q = 0; q < S; ++q)
 #pragma unroll
             for (int o = 0; o < 8; ++o) fo[o][q] = bld<F>(own, voff, L::template soff<F>(o, q));
     }
 
-    // the MUSCL wall-cell path scales the row across every face: 1 where no
-    // wall is (the wall faces' densities follow, after barriers)
-    if constexpr (MU == 2 && !REG) {
+    // the MUSCL step scales the row across every face of a wall cell: 1 where
+    // no wall is (the wall faces' densities follow, after barriers)
+    if constexpr (MU && !REG) {
         if (tid < 6) sm.rho_w[tid] = 1.0;
     }
     // diffuse walls: density of the re-emitted Maxwellian (zero net mass flux)
@@ -1001,8 +1234,12 @@ __device__ __forceinline__ void step_cell(const StepArgs &a, int64_t c, StepSmem
     hook.template apply<F, NH, T>(a, cell, c, fo, sm.red);
 
     double m[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-    if constexpr (MU) {
-        transport_muscl<F, NH, T, MU == 2, kLateOwn, MU == 2 && !REG>(fo, cell, c, own, a, sm.rho_w, dth, m);
+    if constexpr (MU == 1) {
+        __syncthreads();  // the table (and rho_w)
+        transport_muscl_jumps<F, NH, T>(fo, cell, own, a, sm.tab, sm.rho_w, dth, m, &sm.stage[0][0][0],
+                                             sm.park.get());
+    } else if constexpr (MU == 2) {
+        transport_muscl<F, NH, T, !REG>(fo, cell, c, own, a, sm.rho_w, dth, m);
     } else {
         // one row descriptor per face for the main transport pass: the upwind
         // cell's average
@@ -1084,13 +1321,23 @@ __device__ __forceinline__ bool needs_correction(const DevCell *cells, int64_t c
 template <typename F, int NH, int T, int WPE, int FENCE, bool NT, bool MU = false, bool REG = false>
 __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(WPE, 8))) void k_step(StepArgs a) {
     static_assert(T % 64 == 0, "whole waves: the wave sums read every lane");
-    __shared__ StepSmem<F, NH, T> sm;
+    __shared__ StepSmem<F, NH, T, MU> sm;
     const uint32_t b = remap_cell(blockIdx.x, gridDim.x, a.xcd_log2);
     const int64_t c = a.sel ? int64_t(as_const_space(a.sel)[b]) : int64_t(b);
     if constexpr (MU) {
-        if (!muscl_single_row(a.cells, c)) step_cell<F, NH, T, FENCE, NT, 1, false>(a, c, sm);
-        else if (RecRT(a.cells, c).flags() & 1) step_cell<F, NH, T, FENCE, NT, 2, false>(a, c, sm);
-        else step_cell<F, NH, T, FENCE, NT, 2, true>(a, c, sm);
+        // (each path decodes its cell for itself: nothing held for another's sake)
+        int64_t x = c;
+        const StepArgs *pa = &a;
+        if (!muscl_single_row(a.cells, c)) {
+            asm volatile("" : "+s"(x));
+            step_cell<F, NH, T, FENCE, NT, 1, false>(*pa, x, sm);
+        } else if (RecRT(a.cells, c).flags() & 1) {
+            asm volatile("" : "+s"(x));
+            step_cell<F, NH, T, FENCE, NT, 2, false>(*pa, x, sm);
+        } else {
+            asm volatile("" : "+s"(x));
+            step_cell<F, NH, T, FENCE, NT, 2, true>(*pa, x, sm);
+        }
     } else if constexpr (!REG) {
         // every cell in one launch: the reduced code for the cells without
         // FINER or WALL faces, the full code for the others (uniform branch)
@@ -1244,7 +1491,7 @@ __global__ __launch_bounds__(256) void k_wall_den(const F *m1, double *den, VelG
     X(2, 64, 3, 3, 0)        \
     X(4, 64, 3, 3, 0)        \
     X(6, 256, 6, 6, 0)       \
-    X(8, 256, 5, 5, 0)       \
+    X(8, 256, 5, 4, 0)       \
     X(12, 576, 7, 3, 1)
 
 template <typename F>
