@@ -136,8 +136,14 @@ hipError_t launch_fluid_moments(const uint8_t *mask, const double *mom, double *
 // Boltzmann collision integral on Korobov nodes (korobov.hip / korobov.cpp).
 struct KorArgs {
     void *f;                 // [n_cells][NV] post-transport state, updated in place
-    const uint64_t *table;   // [p][NV] entries j | l << 16 | m << 32 | n << 48 (internal indices; 0xFFFF:
-                             // no gain; n = |k_j - k_i|^2 in node units)
+    const int32_t *node;     // [NV] internal node of each slot (by decreasing number of gain trials)
+    const int32_t *row;      // [NV] LDS row of each internal node
+    const int32_t *gain_len; // [NV / 64] list length of each 64 slots, a multiple of 4
+    const int32_t *gain_at;  // [NV / 64] where their lists start
+    const uint64_t *gain;    // entries l | m << 16 | n << 32 ([k][64 slots] per 64 slots; l, m rows,
+                             // n = |k_j - k_i|^2 in node units)
+    const double *freq;      // B's matrix, slots x rows, or NULL (korobov_matrix)
+    const uint32_t *pair;    // else the partners' rows, [p][NV slots]: j | n << 16
     int64_t n_cells;
     int p;
     double w0;               // V_box / p
@@ -146,13 +152,22 @@ struct KorArgs {
     VelGrid g;
     int *flag;               // raised if a conservation system is singular
 };
+// The trials in the device's form, one block for all the tables above.
+struct KorPlan {
+    std::vector<char> host;
+    size_t node = 0, row = 0, gain_len = 0, gain_at = 0, gain = 0, freq = 0, pair = 0;  // byte offsets
+    bool matrix = false;
+};
+// B by a dense matrix product (korobov.hip): its cost does not depend on p, that
+// of gathering p partners does.
+inline bool korobov_matrix(int nh, int64_t p) { return nh == 2 ? p >= 32 : nh == 4 && p >= 128; }
 hipError_t launch_korobov(bool fp64, const KorArgs &a, hipStream_t st);
 bool korobov_supported(int nh);
 int64_t korobov_generator(int64_t p);
 void korobov_tables(int n, double vmax, int64_t p, int64_t a, std::vector<int32_t> &J, std::vector<int32_t> &L,
                     std::vector<int32_t> &M);
-void korobov_device_table(int nh, const std::vector<int32_t> &J, const std::vector<int32_t> &L,
-                          const std::vector<int32_t> &M, int64_t p, std::vector<uint64_t> &out);
+void korobov_plan(int nh, double vmax, const std::vector<int32_t> &J, const std::vector<int32_t> &L,
+                  const std::vector<int32_t> &M, int64_t p, KorPlan &out);
 
 // Lattice Boltzmann subset (lbm.hip / lbm.cpp).
 struct LbmCell {        // 32 bytes per cell

@@ -152,8 +152,8 @@ int dvm_create_solver(const dvm_mesh *m, const dvm_params *p, dvm_solver **out) 
         s->kor_a = kor_a;
         std::vector<int32_t> J, L, M;
         korobov_tables(p->nv, p->vmax[0], s->kor_p, s->kor_a, J, L, M);
-        korobov_device_table(nh, J, L, M, s->kor_p, s->kor_host);
-        o += align256(s->kor_host.size() * sizeof(uint64_t));
+        korobov_plan(nh, p->vmax[0], J, L, M, s->kor_p, s->kor);
+        o += align256(s->kor.host.size());
     }
     s->hybrid = p->hybrid != 0;
     s->off_hyb = o;
@@ -250,8 +250,7 @@ int dvm_upload(dvm_solver *s, void *stream) {
         if (e != hipSuccess) return hip_fail(e, "wall denominators");
     }
     if (s->korobov()) {
-        e = hipMemcpyAsync(s->ws + s->off_kor, s->kor_host.data(), s->kor_host.size() * sizeof(uint64_t),
-                           hipMemcpyHostToDevice, st);
+        e = hipMemcpyAsync(s->ws + s->off_kor, s->kor.host.data(), s->kor.host.size(), hipMemcpyHostToDevice, st);
         if (e != hipSuccess) return hip_fail(e, "Korobov table");
     }
     e = solver_reset_hybrid(s, st);
@@ -343,7 +342,14 @@ int dvm_step(dvm_solver *s, int32_t n_steps, double dt, double cfl, void *stream
         if (s->korobov()) {
             KorArgs k{};
             k.f = a.f_out;
-            k.table = s->kor();
+            const char *plan = s->ws + s->off_kor;
+            k.node = reinterpret_cast<const int32_t *>(plan + s->kor.node);
+            k.row = reinterpret_cast<const int32_t *>(plan + s->kor.row);
+            k.gain_len = reinterpret_cast<const int32_t *>(plan + s->kor.gain_len);
+            k.gain_at = reinterpret_cast<const int32_t *>(plan + s->kor.gain_at);
+            k.gain = reinterpret_cast<const uint64_t *>(plan + s->kor.gain);
+            k.freq = s->kor.matrix ? reinterpret_cast<const double *>(plan + s->kor.freq) : nullptr;
+            k.pair = reinterpret_cast<const uint32_t *>(plan + s->kor.pair);
             k.n_cells = s->n;
             k.p = int(s->kor_p);
             k.w0 = 8.0 * s->p.vmax[0] * s->p.vmax[0] * s->p.vmax[0] / double(s->kor_p);

@@ -36,8 +36,8 @@ struct dvm_solver {
     size_t f_bytes = 0, mom_bytes = 0, tab_bytes = 0, ws_bytes = 0;
     // workspace sections (byte offsets)
     size_t off_gin = 0, off_m1 = 0, off_den = 0, off_flag = 0, off_part = 0, off_sums = 0;
-    size_t off_kor = 0;          // Korobov collision: trial table [p][NV] (64-bit entries)
-    std::vector<uint64_t> kor_host;
+    size_t off_kor = 0;          // Korobov collision: the trials in the device's form
+    dvm::KorPlan kor;
     int64_t kor_p = 0, kor_a = 0;
     size_t off_hyb = 0;          // hybrid: masks (effective, previous, row flags) [n], flux sums [n][66],
                                  // interface face fluxes [n][6][5]
@@ -66,7 +66,6 @@ struct dvm_solver {
 
     void *gin() const { return ws + off_gin; }
     void *m1() const { return ws + off_m1; }
-    const uint64_t *kor() const { return reinterpret_cast<const uint64_t *>(ws + off_kor); }
     bool korobov() const { return p.collision == DVM_COLL_KOROBOV; }
     double *den() const { return reinterpret_cast<double *>(ws + off_den); }
     int *flag() const { return reinterpret_cast<int *>(ws + off_flag); }
