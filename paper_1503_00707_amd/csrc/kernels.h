@@ -29,6 +29,8 @@ struct StepArgs {
     int64_t n_cells;
     double dt;
     double h0;
+    double dt_h0;            // dt / h0
+    double dt_tau;           // dt / tau_or_kn
     VelGrid g;
     int collision;           // DVM_COLL_*
     int tau_mode;            // DVM_TAU_*

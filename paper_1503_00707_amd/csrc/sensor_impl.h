@@ -160,7 +160,7 @@ __global__ __launch_bounds__(T) void k_labels(const F *f, float *r, VelGrid g) {
     const double rho = w * m[0];
     const double u[3] = {w * m[1] / rho, w * m[2] / rho, w * m[3] / rho};
     const double Tt = (2.0 * w * m[4] / rho - (u[0] * u[0] + u[1] * u[1] + u[2] * u[2])) / 3.0;
-    maxwell_tables<F, NH, T>(sm.mx, rho, u, Tt, 1.0, g);
+    maxwell_tables<F, NH, T>(sm.mx, rho, u, Tt, rsqrt_f64(Tt), 1.0, g);
     double s2[2] = {0.0, 0.0};
 #pragma unroll
     for (int q = 0; q < S; ++q) {
@@ -731,7 +731,7 @@ __global__ __launch_bounds__(T) void k_hybrid_rows(StepArgs a, HybArgs h) {
         if (threadIdx.x == 0) *a.flag = 1;
         return;
     }
-    maxwell_tables<F, NH, T>(sm, rho, u, Tt, 1.0, a.g);
+    maxwell_tables<F, NH, T>(sm, rho, u, Tt, rsqrt_f64(Tt), 1.0, a.g);
     F zero[8][Lane<NH, T>::S];
     for (int q = 0; q < Lane<NH, T>::S; ++q)
         for (int o = 0; o < 8; ++o) zero[o][q] = F(0);

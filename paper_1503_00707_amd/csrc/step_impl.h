@@ -90,6 +90,28 @@ __device__ inline double wave_sum(double v) {
     return (readlane_f64(v, 0) + readlane_f64(v, 16)) + (readlane_f64(v, 32) + readlane_f64(v, 48));
 }
 
+// 1/x and 1/sqrt(x) to an ulp or two for normal x: the hardware's estimates
+// refined by two Newton steps, without the exponent scaling of a full division
+// (a third of its instructions; a cell's fixed work has some twenty of them).
+__device__ __forceinline__ double rcp_f64(double x) {
+    double y = __builtin_amdgcn_rcp(x);
+    y = __builtin_fma(y, __builtin_fma(-x, y, 1.0), y);
+    return __builtin_fma(y, __builtin_fma(-x, y, 1.0), y);
+}
+__device__ __forceinline__ double rsqrt_f64(double x) {
+    double y = __builtin_amdgcn_rsq(x);
+    y = __builtin_fma(0.5 * y, __builtin_fma(-x * y, y, 1.0), y);
+    return __builtin_fma(0.5 * y, __builtin_fma(-x * y, y, 1.0), y);
+}
+
+// Sum over a row of 16 lanes; every lane of the row receives it.
+__device__ __forceinline__ double row_sum(double v) {
+    v += dpp_f64<0xb1>(v);
+    v += dpp_f64<0x4e>(v);
+    v += dpp_f64<0x141>(v);
+    return v + dpp_f64<0x140>(v);
+}
+
 // Sum K values over the workgroup; every thread receives the same totals in
 // a fixed combination order (deterministic).
 template <int T, int K>
@@ -98,6 +120,7 @@ __device__ inline void block_sum(double (&v)[K], double *scratch) {
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
 #pragma unroll
     for (int k = 0; k < K; ++k) v[k] = wave_sum(v[k]);
+    if constexpr (NW == 1) return;
     if (lane == 0) {
 #pragma unroll
         for (int k = 0; k < K; ++k) scratch[wid * K + k] = v[k];
@@ -301,57 +324,86 @@ __device__ inline double gram_entry(int i, int j, const double *X, const double 
 // the first wave, one element per lane in a register (G is symmetric
 // positive definite, so no pivoting).  tab[0] carries C * mfac, so that the table
 // product is mfac * Mt.
+// On the small grids this and the moments are most of a step's arithmetic: up
+// to 16 nodes an axis take one row of 16 lanes, and where the workgroup has
+// fewer waves than axes the three share the first wave (one after another
+// before: with the divisions 243,200 cells x 8^3 nodes FP32 took 657 us, now
+// 380; 16^3 cells x 8^3 nodes FP64 28.0 -> 22.7 us with the global sums).
+// isT = 1 / sqrt(Tt).
 template <typename F, int NH, int T>
 __device__ __forceinline__ void maxwell_solve(MaxwellSmem<F, NH> &sm, double rho, const double u[3], double Tt,
-                                              const VelGrid &g) {
+                                              double isT, const VelGrid &g) {
     constexpr int N = 2 * NH;
     constexpr int NW = (T + 63) / 64;
     static_assert(N <= 64, "one wave per axis");
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    for (int b = wid; b < 3; b += NW) {
-        double gk = 0.0, ck = 0.0;
-        if (lane < N) {
-            const double xi = (double(lane - NH) + 0.5) * g.dv[b];
-            ck = (xi - u[b]) / sqrt(Tt);
-            gk = exp(-0.5 * ck * ck);
-            sm.g[b][lane] = gk;
-            sm.c[b][lane] = ck;
+    if constexpr (N <= 16) {
+        constexpr bool kOwnWave = NW >= 3;
+        if (kOwnWave ? wid < 3 : wid == 0) {
+            const int b = kOwnWave ? (lane < 16 ? wid : 3) : lane >> 4, k = lane & 15;
+            const double dv = b == 0 ? g.dv[0] : b == 1 ? g.dv[1] : g.dv[2];
+            const double ub = b == 0 ? u[0] : b == 1 ? u[1] : u[2];
+            double p[5];
+            const double ck = ((double(k - NH) + 0.5) * dv - ub) * isT;
+            p[0] = exp(-0.5 * ck * ck);
+            if (b < 3 && k < N) {
+                sm.g[b][k] = p[0];
+                sm.c[b][k] = ck;
+            } else {
+                p[0] = 0.0;
+            }
+#pragma unroll
+            for (int q = 1; q < 5; ++q) p[q] = p[q - 1] * ck;
+#pragma unroll
+            for (int q = 0; q < 5; ++q) p[q] = row_sum(p[q]);
+            if (b < 3 && k == 0)
+                for (int q = 0; q < 5; ++q) sm.S[5 * b + q] = p[q] * dv;
         }
-        double p[5];
-        p[0] = gk;
+    } else {
+        for (int b = wid; b < 3; b += NW) {
+            double gk = 0.0, ck = 0.0;
+            if (lane < N) {
+                const double xi = (double(lane - NH) + 0.5) * g.dv[b];
+                ck = (xi - u[b]) * isT;
+                gk = exp(-0.5 * ck * ck);
+                sm.g[b][lane] = gk;
+                sm.c[b][lane] = ck;
+            }
+            double p[5];
+            p[0] = gk;
 #pragma unroll
-        for (int q = 1; q < 5; ++q) p[q] = p[q - 1] * ck;
+            for (int q = 1; q < 5; ++q) p[q] = p[q - 1] * ck;
 #pragma unroll
-        for (int q = 0; q < 5; ++q) p[q] = wave_sum(p[q]);
-        if (lane == 0)
-            for (int q = 0; q < 5; ++q) sm.S[5 * b + q] = p[q] * g.dv[b];
+            for (int q = 0; q < 5; ++q) p[q] = wave_sum(p[q]);
+            if (lane == 0)
+                for (int q = 0; q < 5; ++q) sm.S[5 * b + q] = p[q] * g.dv[b];
+        }
     }
     __syncthreads();
     if (wid == 0) {
         const int i = lane / 6, j = lane % 6;
         const bool el = lane < 30;
-        const double x2 = 6.283185307179586476925286766559 * Tt;
-        const double C = rho / (x2 * sqrt(x2));
+        const double n32 = 15.749609945722419 * Tt * (Tt * isT);  // (2 pi T)^(3/2)
         // lane 6i + j holds A[i][j]; each elimination step reads the pivot
         // row and column from the lanes that hold them (no LDS round trip)
         double x = 0.0;
         if (el) {
             if (j < 5) x = gram_entry(i, j, &sm.S[0], &sm.S[5], &sm.S[10]);
             else {
-                const double t = (i == 0 ? 1.0 : i == 4 ? 3.0 : 0.0) * (rho / C);
+                const double t = (i == 0 ? 1.0 : i == 4 ? 3.0 : 0.0) * n32;
                 x = t - gram_entry(i, 0, &sm.S[0], &sm.S[5], &sm.S[10]);
             }
         }
 #pragma unroll
         for (int k = 0; k < 5; ++k) {
-            const double akk = readlane_f64(x, 7 * k);
+            const double r = rcp_f64(readlane_f64(x, 7 * k));
             const double aik = shfl_f64(x, 6 * i + k);
             const double akj = shfl_f64(x, 6 * k + j);
-            if (el && i != k) x = x - aik / akk * akj;
+            if (el && i != k) x = x - aik * r * akj;
         }
         const double diag = shfl_f64(x, 7 * lane), rhs = shfl_f64(x, 6 * lane + 5);
-        if (lane < 5) sm.d[lane] = rhs / diag;
-        if (lane == 0) sm.C = C;
+        if (lane < 5) sm.d[lane] = rhs * rcp_f64(diag);
+        if (lane == 0) sm.C = rho * rcp_f64(n32);
     }
     __syncthreads();
 }
@@ -363,23 +415,25 @@ __device__ void maxwell_fill(MaxwellSmem<F, NH> &sm, double mfac) {
     constexpr int N = 2 * NH;
     constexpr int NW = (T + 63) / 64;
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    for (int b = wid; b < 3; b += NW) {
-        if (lane < N) {
-            const double cc = sm.c[b][lane];
-            const double P = b == 0 ? 1.0 + sm.d[0] + sm.d[1] * cc + sm.d[4] * cc * cc
-                                    : sm.d[1 + b] * cc + sm.d[4] * cc * cc;
-            const double G = b == 0 ? sm.g[b][lane] * sm.C * mfac : sm.g[b][lane];
-            sm.tab[b][lane][0] = F(G);
-            sm.tab[b][lane][1] = F(P);
-        }
+    const auto fill = [&](int b, int k) {
+        const double cc = sm.c[b][k], db = sm.d[1 + b] * cc + sm.d[4] * cc * cc;
+        sm.tab[b][k][0] = F(b == 0 ? sm.g[b][k] * sm.C * mfac : sm.g[b][k]);
+        sm.tab[b][k][1] = F(b == 0 ? 1.0 + sm.d[0] + db : db);
+    };
+    if constexpr (N <= 16) {
+        const int b = NW >= 3 ? (lane < 16 ? wid : 3) : wid == 0 ? lane >> 4 : 3;
+        if (b < 3 && (lane & 15) < N) fill(b, lane & 15);
+    } else {
+        for (int b = wid; b < 3; b += NW)
+            if (lane < N) fill(b, lane);
     }
     __syncthreads();
 }
 
 template <typename F, int NH, int T>
 __device__ __forceinline__ void maxwell_tables(MaxwellSmem<F, NH> &sm, double rho, const double u[3], double Tt,
-                                               double mfac, const VelGrid &g) {
-    maxwell_solve<F, NH, T>(sm, rho, u, Tt, g);
+                                               double isT, double mfac, const VelGrid &g) {
+    maxwell_solve<F, NH, T>(sm, rho, u, Tt, isT, g);
     maxwell_fill<F, NH, T>(sm, mfac);
 }
 
@@ -1175,7 +1229,7 @@ __device__ __forceinline__ void step_cell(const StepArgs &a, int64_t c, StepSmem
     const F *fin = static_cast<const F *>(a.f_in);
     constexpr uint32_t kRow = uint32_t(NV * sizeof(F));
     const Rsrc own = rsrc(fin + c * NV, kRow);
-    const double dth = a.dt / (a.h0 / double(1 << cell.level()));
+    const double dth = a.dt_h0 * double(1 << cell.level());  // (exact: a power of two)
 
     // own values of every slot and octant, kept in registers for the step.
     // Reduced path: loaded octant by octant inside the transport pass, with
@@ -1264,10 +1318,10 @@ __device__ __forceinline__ void step_cell(const StepArgs &a, int64_t c, StepSmem
     block_sum<T, 5>(m, sm.red);
 
     const double w = a.g.w;
-    const double rho = w * m[0];
-    const double u[3] = {w * m[1] / rho, w * m[2] / rho, w * m[3] / rho};
+    const double rho = w * m[0], ir = rcp_f64(rho);
+    const double u[3] = {w * m[1] * ir, w * m[2] * ir, w * m[3] * ir};
     const double E = w * m[4];
-    const double Tt = (2.0 * E / rho - (u[0] * u[0] + u[1] * u[1] + u[2] * u[2])) / 3.0;
+    const double Tt = (2.0 * E * ir - (u[0] * u[0] + u[1] * u[1] + u[2] * u[2])) * (1.0 / 3.0);
     const bool bad = !(rho > 0.0) || !(Tt > 0.0);
     if (tid == 0) {
         const int64_t n = a.n_cells;
@@ -1288,16 +1342,12 @@ __device__ __forceinline__ void step_cell(const StepArgs &a, int64_t c, StepSmem
         }
         return;
     }
-    const double tau = a.tau_mode == DVM_TAU_HS ? a.tau_or_kn / (rho * sqrt(Tt)) : a.tau_or_kn;
-    double e, mfac;
-    if (a.collision == DVM_COLL_EULER) {
-        e = 1.0 - a.dt / tau;
-        mfac = a.dt / tau;
-    } else {
-        e = exp(-a.dt / tau);
-        mfac = -expm1(-a.dt / tau);
-    }
-    maxwell_tables<F, NH, T>(sm.mx, rho, u, Tt, mfac, a.g);
+    const double isT = rsqrt_f64(Tt);
+    const double x = a.tau_mode == DVM_TAU_HS ? a.dt_tau * (rho * (Tt * isT)) : a.dt_tau;  // dt / tau
+    // explicit Euler: f + x (Mt - f); exponential: Mt + e^{-x} (f - Mt)
+    const double mfac = a.collision == DVM_COLL_EULER ? x : -expm1(-x);
+    const double e = 1.0 - mfac;
+    maxwell_tables<F, NH, T>(sm.mx, rho, u, Tt, isT, mfac, a.g);
     relax_store<F, NH, T, NT>(sm.mx, fo, F(e), out);
 }
 
@@ -1395,7 +1445,7 @@ __global__ __launch_bounds__(T) void k_init(InitArgs a) {
         for (int b = 0; b < 3; ++b) a.mom[(1 + b) * a.n + c] = rho * u[b];
         a.mom[4 * a.n + c] = 0.5 * rho * (u[0] * u[0] + u[1] * u[1] + u[2] * u[2]) + 1.5 * rho * Tt;
     }
-    maxwell_tables<F, NH, T>(sm, rho, u, Tt, 1.0, a.g);
+    maxwell_tables<F, NH, T>(sm, rho, u, Tt, rsqrt_f64(Tt), 1.0, a.g);
     F zero[8][S];
 #pragma unroll
     for (int q = 0; q < S; ++q)
