@@ -16,7 +16,12 @@ namespace {
 constexpr size_t kScratchGrad = (size_t(kTrainBlocks) * kMlpWeights * sizeof(double) + 255) & ~size_t(255);
 constexpr size_t kScratchLoss = (size_t(kTrainBlocks) * sizeof(double) + 255) & ~size_t(255);
 constexpr int kMaxDevices = 64;
-constexpr int64_t kSensorSmallMesh = 65536;
+// Up to these sizes the sensor runs with 16 lanes per cell, above with a
+// thread per cell: the first is bound by the latency of one tile, the second
+// by the tiles' number.  Network, 16 lanes / a thread per cell: 16,384 cells
+// 11.9 / 27.3 us, 32,768: 19.0 / 27.8, 65,536: 32.4 / 29.0, 1e6: 407 / 196.
+// Gradient length: 16,384 cells 8.8 / 8.9, 32,768: 10.9 / 9.2, 1e6: 253 / 100.
+constexpr int64_t kSensorSmallNet = 49152, kSensorSmallKn = 16384;
 }  // namespace
 static __device__ __align__(256) char scratch[kScratchGrad + kScratchLoss];
 
@@ -65,18 +70,17 @@ hipError_t launch_mlp_forward(const float *params, const float *x, int64_t n, in
     if (mode == 0)
         hipLaunchKernelGGL(impl::k_mlp_fwd32, dim3(unsigned((n + 255) / 256)), dim3(256), 0, st, params, x, n, z);
     else
-        hipLaunchKernelGGL(impl::k_mlp_fwd_mfma, dim3(unsigned((n + 63) / 64)), dim3(256), 0, st, params, x, n, z);
+        hipLaunchKernelGGL(impl::k_mlp_fwd_mfma, dim3(unsigned(n < 16 * 2048 ? (n + 15) / 16 : 2048)), dim3(256), 0, st, params, x, n, z);
     return hipGetLastError();
 }
 
 hipError_t launch_sensor(const SensorArgsPub &a, const float *params, double kappa, uint8_t *mask, float *score,
                          hipStream_t st) {
-    // below 1024 workgroups of 64 cells, one-wave workgroups of 16 cells
-    if (a.n <= kSensorSmallMesh)
-        hipLaunchKernelGGL(impl::k_sensor<16>, dim3(unsigned((a.n + 15) / 16)), dim3(64), 0, st, feat(a), params,
+    if (a.n <= (params ? kSensorSmallNet : kSensorSmallKn))
+        hipLaunchKernelGGL(impl::k_sensor<16>, dim3(unsigned((a.n + 15) / 16)), dim3(256), 0, st, feat(a), params,
                            kappa, mask, score);
     else
-        hipLaunchKernelGGL(impl::k_sensor<64>, dim3(unsigned((a.n + 63) / 64)), dim3(256), 0, st, feat(a), params,
+        hipLaunchKernelGGL(impl::k_sensor<256>, dim3(unsigned((a.n + 255) / 256)), dim3(256), 0, st, feat(a), params,
                            kappa, mask, score);
     return hipGetLastError();
 }
@@ -131,7 +135,7 @@ hipError_t launch_norm_stats(const float *x, int64_t n, float *params, hipStream
 }
 
 hipError_t launch_mask_eff(const uint8_t *in, uint8_t *out, const DevCell *cells, int64_t n, hipStream_t st) {
-    hipLaunchKernelGGL(impl::k_mask_eff, dim3(unsigned((n + 255) / 256)), dim3(256), 0, st, in, out, cells, n);
+    hipLaunchKernelGGL(impl::k_mask_eff, dim3(unsigned((n + 63) / 64)), dim3(64), 0, st, in, out, cells, n);
     return hipGetLastError();
 }
 

@@ -112,6 +112,18 @@ __device__ __forceinline__ double row_sum(double v) {
     return v + dpp_f64<0x140>(v);
 }
 
+__device__ __forceinline__ float row_sum32(float v) {
+    const auto add = [&](auto ctrl) {
+        v += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), decltype(ctrl)::value, 0xf,
+                                                                0xf, false));
+    };
+    add(std::integral_constant<int, 0xb1>{});
+    add(std::integral_constant<int, 0x4e>{});
+    add(std::integral_constant<int, 0x141>{});
+    add(std::integral_constant<int, 0x140>{});
+    return v;
+}
+
 // Sum K values over the workgroup; every thread receives the same totals in
 // a fixed combination order (deterministic).
 template <int T, int K>
@@ -1209,7 +1221,7 @@ __device__ __forceinline__ void transport_muscl_jumps(Regs<F, NH, T> &fo, const 
 // the transport overwrites them (the hybrid step records interface fluxes).
 struct NoHook {
     template <typename F, int NH, int T>
-    __device__ __forceinline__ void apply(const StepArgs &, const CellView &, int64_t, const Regs<F, NH, T> &,
+    __device__ __forceinline__ void apply(const StepArgs &, int64_t, const Regs<F, NH, T> &,
                                           double *) const {}
 };
 
@@ -1285,7 +1297,7 @@ __device__ __forceinline__ void step_cell(const StepArgs &a, int64_t c, StepSmem
         __syncthreads();
     }
 
-    hook.template apply<F, NH, T>(a, cell, c, fo, sm.red);
+    hook.template apply<F, NH, T>(a, c, fo, sm.red);
 
     double m[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
     if constexpr (MU == 1) {
