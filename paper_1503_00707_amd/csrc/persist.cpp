@@ -116,7 +116,7 @@ hipError_t trial_step(const dvm_solver *s, const StepConfig &cfg, double dt, hip
     while ((1 << (a.xcd_log2 + 1)) <= cfg.xcd_group) ++a.xcd_log2;
     a.f_in = s->f[s->cur];
     a.f_out = s->f[s->cur ^ 1];
-    return launch_step(s->fp64, a, cfg, st);
+    return enqueue_step(s, a, cfg, st);
 }
 
 }  // namespace
@@ -235,6 +235,7 @@ int dvm_tune(dvm_solver *s, const char *cache_path, int32_t reps, int32_t *from_
         s->cfg.wpe = c.wpe;
         s->cfg.xcd_group = c.xcd_group;
         s->cfg.nt_store = c.nt_store != 0;
+        s->cfg_default = false;
         if (from_cache) *from_cache = 1;
         return DVM_OK;
     }
@@ -284,6 +285,7 @@ int dvm_tune(dvm_solver *s, const char *cache_path, int32_t reps, int32_t *from_
     s->cfg.wpe = best_cfg.wpe;
     s->cfg.xcd_group = best_cfg.xcd_group;
     s->cfg.nt_store = best_cfg.nt_store;
+    s->cfg_default = false;
     return tune_cache_put(cache_path, key, best_cfg, best);
 }
 

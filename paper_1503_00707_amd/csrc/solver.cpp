@@ -3,6 +3,7 @@
 // every buffer is bound by the caller (dvm_bind).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <new>
@@ -14,11 +15,68 @@ using namespace dvm;
 namespace {
 // two launches (reduced kernel over the regular cells, full kernel over the
 // rest) instead of one: first order, kernels compiled
-bool use_split(const dvm_solver *s) {
-    return s->split && !s->muscl && s->n_reg > 0 && have_regular_kernel(s->nh, s->cfg.threads, s->cfg.wpe) &&
+bool use_split(const dvm_solver *s, const StepConfig &cfg) {
+    return s->split && !s->muscl && s->n_reg > 0 && have_regular_kernel(s->nh, cfg.threads, cfg.wpe) &&
            have_kernel(s->nh, s->cfg_irr.threads, s->cfg_irr.wpe);
 }
+
+// The FP64 default at 24^3 nodes (576 threads, wpe 30) steps the regular cells
+// with 192 threads at two waves per SIMD and the others with 576 at five,
+// unless dvm_tune_split has set one or two launches.  Regular cells hold three
+// times the loads in flight per wave that way (27,000 of them: 1,962 -> 1,581
+// us); the correction pass over the four rows behind a FINER face wants the
+// wide workgroup (30,400 cells, 16 % with such faces: one launch at 576
+// threads 2,555 us, at 192 threads 2,663, two launches 2,317; 570 cells: 71,
+// 128, 71).  FP32 keeps one launch: 420,251 cells 12.5 ms against 14.0.
+bool two_shapes(const dvm_solver *s, const StepConfig &cfg) {
+    return s->fp64 && s->nh == 12 && !s->muscl && !s->split_set && s->n_reg > 0 && cfg.threads == 576 &&
+           (cfg.wpe == 30 || cfg.wpe == 0);
+}
 }  // namespace
+
+void dvm::default_grouping(StepConfig &c, int nh, int64_t n, double state_bytes) {
+    // Consecutive cells share upwind rows, so each XCD takes runs of them.
+    // Group 1 / 64 on 30,400 cells FP64: 16^3 nodes 700 / 565 us, 12^3 329 /
+    // 294, 8^3 101 / 83; FP32 8^3, 243,200 cells: 421 / 365.  24^3 nodes: runs
+    // of 32, whose rows fit the XCD's L2 (FP32, 420,251 cells, 512 / 128 / 32
+    // / 8: 12.51 / 12.37 / 12.31 / 12.73 ms; 3,800 cells, 512 / 16: 175 / 141
+    // us; FP64, 30,400 cells, 64 / 32: 2,340 / 2,317 us).  A round over the
+    // XCDs has to fit the mesh: at most n / 8.
+    int64_t g = nh == 12 ? 32 : 64;
+    g = std::min(g, std::max<int64_t>(1, n / 8));
+    c.xcd_group = 1;
+    while (2 * c.xcd_group <= g) c.xcd_group *= 2;
+    // Non-temporal stores once the two state buffers exceed the 256 MB
+    // Infinity Cache; below, the next step finds its rows there (FP64 16^3
+    // nodes, 3,800 cells of 124 MB: 84 -> 75 us; 24^3, 1,590 cells of 176 MB:
+    // 153 us with, 177 without).
+    c.nt_store = state_bytes > 128.0 * (1 << 20);
+}
+
+hipError_t dvm::enqueue_step(const dvm_solver *s, const StepArgs &a, const StepConfig &cfg, hipStream_t st) {
+    StepConfig reg = cfg, irr = cfg;  // stores and grouping as chosen; its own shapes
+    if (use_split(s, cfg)) {
+        irr.threads = s->cfg_irr.threads;
+        irr.wpe = s->cfg_irr.wpe;
+    } else if (two_shapes(s, cfg)) {
+        reg.threads = 192;
+        reg.wpe = 21;
+        irr.threads = 576;
+        irr.wpe = 51;
+    } else {
+        return launch_step(s->fp64, a, cfg, st);
+    }
+    reg.regular = 1;
+    irr.regular = 0;
+    StepArgs part = a;
+    part.sel = s->sel();
+    part.n_sel = s->n_reg;
+    hipError_t e = launch_step(s->fp64, part, reg, st);
+    if (e != hipSuccess || s->n == s->n_reg) return e;
+    part.sel = s->sel() + s->n_reg;
+    part.n_sel = s->n - s->n_reg;
+    return launch_step(s->fp64, part, irr, st);
+}
 
 StepArgs dvm::solver_step_args(const dvm_solver *s, double dt) {
     StepArgs a{};
@@ -103,28 +161,21 @@ int dvm_create_solver(const dvm_mesh *m, const dvm_params *p, dvm_solver **out) 
     }
     // measured defaults per (precision, N); dvm_tune_set overrides them
     s->cfg.threads = thr;
-    s->cfg.xcd_group = 1;
-    s->cfg.nt_store = 0;
     s->cfg.wpe = 0;
+    default_grouping(s->cfg, nh, s->n, double(s->n) * double(s->nv) * (fp64 ? 8 : 4));
     if (nh == 12 && !fp64) {
         s->cfg.threads = 192;
         s->cfg.wpe = 31;
-        s->cfg.xcd_group = 512;
-        s->cfg.nt_store = 1;
     }
     if ((nh == 6 || nh == 8) && !fp64) {
         // 12^3 and 16^3: per-cell fixed work (reductions, the Maxwellian
         // system) dominates, and two waves per cell keep more cells in flight
         s->cfg.threads = 128;
         s->cfg.wpe = nh == 6 ? 60 : 50;
-        s->cfg.xcd_group = 64;
-        s->cfg.nt_store = 1;
     }
     if (nh == 12 && fp64) {
         s->cfg.threads = 576;
         s->cfg.wpe = 30;
-        s->cfg.xcd_group = 64;
-        s->cfg.nt_store = 1;
     }
     if (m->device_tables) {
         // no solid leaves: domain faces are the only INFLOW / WALL faces
@@ -320,26 +371,7 @@ int dvm_step(dvm_solver *s, int32_t n_steps, double dt, double cfl, void *stream
     for (int it = 0; it < n_steps; ++it) {
         a.f_in = s->f[s->cur];
         a.f_out = s->f[s->cur ^ 1];
-        if (use_split(s)) {
-            StepArgs ar = a;
-            ar.sel = s->sel();
-            ar.n_sel = s->n_reg;
-            StepConfig cr = s->cfg;
-            cr.regular = 1;
-            e = s->n_reg > 0 ? launch_step(s->fp64, ar, cr, st) : hipSuccess;
-            if (e == hipSuccess && s->n > s->n_reg) {
-                StepArgs ai = a;
-                ai.sel = s->sel() + s->n_reg;
-                ai.n_sel = s->n - s->n_reg;
-                StepConfig ci = s->cfg;  // stores and grouping as chosen; its own shape
-                ci.threads = s->cfg_irr.threads;
-                ci.wpe = s->cfg_irr.wpe;
-                ci.regular = 0;
-                e = launch_step(s->fp64, ai, ci, st);
-            }
-        } else {
-            e = launch_step(s->fp64, a, s->cfg, st);
-        }
+        e = enqueue_step(s, a, s->cfg, st);
         if (e != hipSuccess) return hip_fail(e, "step");
         if (s->korobov()) {
             KorArgs k{};
@@ -469,6 +501,7 @@ int dvm_tune_set(dvm_solver *s, int32_t threads, int32_t wpe, int32_t xcd_group,
     s->cfg.wpe = wpe;
     s->cfg.xcd_group = xcd_group;
     s->cfg.nt_store = nt_store != 0;
+    s->cfg_default = false;
     return DVM_OK;
 }
 
@@ -495,6 +528,7 @@ int dvm_tune_split(dvm_solver *s, int32_t enable, int32_t threads_irr, int32_t w
         s->cfg_irr.wpe = wpe_irr;
     }
     s->split = enable != 0;
+    s->split_set = true;
     return DVM_OK;
 }
 

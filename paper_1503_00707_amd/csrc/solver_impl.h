@@ -58,7 +58,8 @@ struct dvm_solver {
     // WALL faces ("regular") in a reduced kernel and the others in a second
     // launch (off by default: one launch takes the reduced code path per cell
     // and keeps Morton locality between the two kinds)
-    bool split = false;
+    bool split = false, split_set = false;  // split_set: dvm_tune_split has chosen
+    bool cfg_default = true;                // cfg as dvm_create set it
     int64_t n_reg = 0;             // regular cells: the first n_reg entries of the selection list
     size_t off_sel = 0;            // selection list [n] (regular cells, then the others; Morton order)
     std::vector<uint32_t> sel_host;
@@ -94,6 +95,10 @@ struct dvm_mlp {
 namespace dvm {
 // Kernel arguments of one fused step of size dt (f_in / f_out left NULL).
 StepArgs solver_step_args(const dvm_solver *s, double dt);
+// one step of the solver with shape cfg, a complete: one launch or two
+hipError_t enqueue_step(const dvm_solver *s, const StepArgs &a, const StepConfig &cfg, hipStream_t st);
+// default runs of cells per XCD and kind of stores for n cells (state_bytes: one state buffer)
+void default_grouping(StepConfig &c, int nh, int64_t n, double state_bytes);
 double solver_max_speed_sum(const dvm_solver *s);
 // f[cur] was replaced from outside the step (a remap): records, hybrid masks
 // and the moments buffer describe the new state

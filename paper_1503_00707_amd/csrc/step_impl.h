@@ -1546,6 +1546,8 @@ __global__ __launch_bounds__(256) void k_wall_den(const F *m1, double *den, VelG
     X(6, 256, 6, 0)        \
     X(8, 256, 5, 0)        \
     X(12, 192, 3, 1)
+// FP64 only
+#define DVM_REG_CONFIGS_F64(X) X(12, 192, 2, 1)
 
 // MUSCL step kernels: one shape per N, (NH, threads, waves per EU for FP32
 // and for FP64 storage, octant fence)
@@ -1568,6 +1570,9 @@ hipError_t step_dispatch(const StepArgs &a, const StepConfig &cfg, hipStream_t s
             return hipGetLastError();                                                                       \
         }
         DVM_REG_CONFIGS(X)
+        if constexpr (std::is_same<F, double>::value) {
+            DVM_REG_CONFIGS_F64(X)
+        }
 #undef X
         return hipErrorInvalidValue;
     }
