@@ -282,7 +282,10 @@ int dvm_tune_get(const dvm_solver *s, int32_t *threads, int32_t *wpe, int32_t *x
  * (enable = 1), or every cell in one launch (enable = 0, the default; each
  * workgroup takes the reduced code path when its cell allows it).  Both
  * compute the same step, bitwise: the reduced code only leaves out the passes
- * that such cells skip anyway.  threads_irr > 0 also
+ * that such cells skip anyway.  (The shape (192, 21) of FP64 at 24^3 nodes,
+ * the default there, is such a pair of launches by itself; a batch takes
+ * (576, 30) in its place, and so does dvm_step once this has been called
+ * with enable >= 0.)  threads_irr > 0 also
  * chooses the shape (threads per workgroup, waves-per-EU variant as listed by
  * dvm_tune_shapes) of the second launch; DVM_ERR_UNSUPPORTED if it does not
  * exist.  enable < 0 only queries; *previous (may be NULL) receives the
@@ -293,7 +296,7 @@ int dvm_tune_split(dvm_solver *s, int32_t enable, int32_t threads_irr, int32_t w
 
 /*
  * dvm_tune -- project autotuner for one solver: time every
- * compiled step shape x XCD cell grouping {1, 8, 64, 512} x store kind (plain
+ * compiled step shape x XCD cell grouping {1, 8, 32, 64, 512} x store kind (plain
  * or non-temporal) with reps trial steps on the solver's own state, keep the
  * fastest (dvm_tune_get reports it).  cache_path (may be NULL) names a text
  * file of tuned shapes, one line per key ("step", GPU architecture, N/2,

@@ -229,7 +229,7 @@ int dvm_tune(dvm_solver *s, const char *cache_path, int32_t reps, int32_t *from_
     if (reps < 1) return fail(DVM_ERR_ARG, "reps must be >= 1");
     const TuneKey key{"step", s->nh, s->fp64 ? 1 : 0, s->muscl ? 1 : 0};
     StepConfig c{};
-    if (tune_cache_get(cache_path, key, &c, nullptr) && have_kernel(s->nh, c.threads, c.wpe) && c.xcd_group >= 1 &&
+    if (tune_cache_get(cache_path, key, &c, nullptr) && have_shape(s, c.threads, c.wpe) && c.xcd_group >= 1 &&
         c.xcd_group <= 4096 && !(c.xcd_group & (c.xcd_group - 1))) {
         s->cfg.threads = c.threads;
         s->cfg.wpe = c.wpe;
@@ -251,8 +251,8 @@ int dvm_tune(dvm_solver *s, const char *cache_path, int32_t reps, int32_t *from_
         return fail(DVM_ERR_DEVICE, "events");
     }
     int thr[64], wpe[64];
-    const int nk = std::min(list_kernels(s->nh, thr, wpe, 64), 64);
-    const int groups[4] = {1, 8, 64, 512};
+    const int nk = std::min(list_shapes(s, thr, wpe, 64), 64);
+    const int groups[5] = {1, 8, 32, 64, 512};
     double best = 1e300;
     StepConfig best_cfg = s->cfg;
     for (int k = 0; k < nk && rc == DVM_OK; ++k)

@@ -20,17 +20,16 @@ bool use_split(const dvm_solver *s, const StepConfig &cfg) {
            have_kernel(s->nh, s->cfg_irr.threads, s->cfg_irr.wpe);
 }
 
-// The FP64 default at 24^3 nodes (576 threads, wpe 30) steps the regular cells
-// with 192 threads at two waves per SIMD and the others with 576 at five,
-// unless dvm_tune_split has set one or two launches.  Regular cells hold three
+// The FP64 default at 24^3 nodes, shape (192, 21): the regular cells with 192
+// threads at two waves per SIMD in one launch and the others with 576 at five
+// in a second.  Regular cells hold three
 // times the loads in flight per wave that way (27,000 of them: 1,962 -> 1,581
 // us); the correction pass over the four rows behind a FINER face wants the
 // wide workgroup (30,400 cells, 16 % with such faces: one launch at 576
 // threads 2,555 us, at 192 threads 2,663, two launches 2,317; 570 cells: 71,
 // 128, 71).  FP32 keeps one launch: 420,251 cells 12.5 ms against 14.0.
 bool two_shapes(const dvm_solver *s, const StepConfig &cfg) {
-    return s->fp64 && s->nh == 12 && !s->muscl && !s->split_set && s->n_reg > 0 && cfg.threads == 576 &&
-           (cfg.wpe == 30 || cfg.wpe == 0);
+    return has_two_shapes(s) && cfg.threads == kTwoShapes.threads && cfg.wpe == kTwoShapes.wpe;
 }
 }  // namespace
 
@@ -59,10 +58,14 @@ hipError_t dvm::enqueue_step(const dvm_solver *s, const StepArgs &a, const StepC
         irr.threads = s->cfg_irr.threads;
         irr.wpe = s->cfg_irr.wpe;
     } else if (two_shapes(s, cfg)) {
-        reg.threads = 192;
-        reg.wpe = 21;
         irr.threads = 576;
         irr.wpe = 51;
+        // no regular cell, or dvm_tune_split has been called: its two settings
+        // are the same step bitwise, in one launch (no reduced kernel at 576)
+        if (s->n_reg == 0 || s->split_set) {
+            irr.wpe = kOneShape.wpe;
+            return launch_step(s->fp64, a, irr, st);
+        }
     } else {
         return launch_step(s->fp64, a, cfg, st);
     }
@@ -174,8 +177,9 @@ int dvm_create_solver(const dvm_mesh *m, const dvm_params *p, dvm_solver **out) 
         s->cfg.wpe = nh == 6 ? 60 : 50;
     }
     if (nh == 12 && fp64) {
-        s->cfg.threads = 576;
-        s->cfg.wpe = 30;
+        const ShapeId d = p->scheme == DVM_SCHEME_MUSCL ? kOneShape : kTwoShapes;
+        s->cfg.threads = d.threads;
+        s->cfg.wpe = d.wpe;
     }
     if (m->device_tables) {
         // no solid leaves: domain faces are the only INFLOW / WALL faces
@@ -481,7 +485,7 @@ int dvm_tune_shapes(const dvm_solver *s, int32_t *threads, int32_t *wpe, int32_t
     clear_error();
     if (!s || !n || (cap > 0 && (!threads || !wpe))) return fail(DVM_ERR_ARG, "null argument");
     int t[64], w[64];
-    const int total = list_kernels(s->nh, t, w, 64);
+    const int total = list_shapes(s, t, w, 64);
     for (int k = 0; k < total && k < cap && k < 64; ++k) {
         threads[k] = t[k];
         wpe[k] = w[k];
@@ -495,7 +499,7 @@ int dvm_tune_set(dvm_solver *s, int32_t threads, int32_t wpe, int32_t xcd_group,
     if (!s) return fail(DVM_ERR_ARG, "null solver");
     if (xcd_group < 1 || xcd_group > 4096 || (xcd_group & (xcd_group - 1)))
         return fail(DVM_ERR_ARG, "xcd_group must be a power of two in [1, 4096]");
-    if (!have_kernel(s->nh, threads, wpe))
+    if (!have_shape(s, threads, wpe))
         return fail(DVM_ERR_UNSUPPORTED, "no step kernel with %d threads, wpe %d for N = %d", threads, wpe, 2 * s->nh);
     s->cfg.threads = threads;
     s->cfg.wpe = wpe;

@@ -57,7 +57,8 @@ struct dvm_solver {
     // first order: optionally step the cells without FINER or
     // WALL faces ("regular") in a reduced kernel and the others in a second
     // launch (off by default: one launch takes the reduced code path per cell
-    // and keeps Morton locality between the two kinds)
+    // and keeps Morton locality between the two kinds; FP64 at 24^3 nodes
+    // takes two unless told otherwise)
     bool split = false, split_set = false;  // split_set: dvm_tune_split has chosen
     bool cfg_default = true;                // cfg as dvm_create set it
     int64_t n_reg = 0;             // regular cells: the first n_reg entries of the selection list
@@ -95,6 +96,30 @@ struct dvm_mlp {
 namespace dvm {
 // Kernel arguments of one fused step of size dt (f_in / f_out left NULL).
 StepArgs solver_step_args(const dvm_solver *s, double dt);
+// FP64 at 24^3 nodes, first order: the shape of two launches, and the shape of
+// the one launch over every cell that a batch takes in its place
+struct ShapeId {
+    int threads, wpe;
+};
+constexpr ShapeId kTwoShapes{192, 21}, kOneShape{576, 30};
+inline bool has_two_shapes(const dvm_solver *s) { return s->fp64 && s->nh == 12 && !s->muscl; }
+// a shape that dvm_step takes
+inline bool have_shape(const dvm_solver *s, int threads, int wpe) {
+    return have_kernel(s->nh, threads, wpe) ||
+           (has_two_shapes(s) && threads == kTwoShapes.threads && wpe == kTwoShapes.wpe);
+}
+// the shapes dvm_step takes (at most cap written); returns their number
+inline int list_shapes(const dvm_solver *s, int *threads, int *wpe, int cap) {
+    int n = list_kernels(s->nh, threads, wpe, cap);
+    if (has_two_shapes(s)) {
+        if (n < cap) {
+            threads[n] = kTwoShapes.threads;
+            wpe[n] = kTwoShapes.wpe;
+        }
+        ++n;
+    }
+    return n;
+}
 // one step of the solver with shape cfg, a complete: one launch or two
 hipError_t enqueue_step(const dvm_solver *s, const StepArgs &a, const StepConfig &cfg, hipStream_t st);
 // default runs of cells per XCD and kind of stores for n cells (state_bytes: one state buffer)

@@ -340,7 +340,8 @@ __device__ inline double gram_entry(int i, int j, const double *X, const double 
 // to 16 nodes an axis take one row of 16 lanes, and where the workgroup has
 // fewer waves than axes the three share the first wave (one after another
 // before: with the divisions 243,200 cells x 8^3 nodes FP32 took 657 us, now
-// 380; 16^3 cells x 8^3 nodes FP64 28.0 -> 22.7 us with the global sums).
+// 342; 16^3 cells x 8^3 nodes FP64 28.0 -> 19.7 us with the global sums; 380
+// and 22.7 before the cells went over the XCDs in runs).
 // isT = 1 / sqrt(Tt).
 template <typename F, int NH, int T>
 __device__ __forceinline__ void maxwell_solve(MaxwellSmem<F, NH> &sm, double rho, const double u[3], double Tt,
@@ -1046,8 +1047,9 @@ __device__ __forceinline__ void transport_muscl(Regs<F, NH, T> &fo, const CellVi
 // compute unit.  Walking the neighbours' records per octant and axis instead
 // cost 24 chains of dependent scalar loads a cell, paid by every cell with a
 // level jump within two hops (31 % to 95 % of the cells of these meshes):
-//   Mach-2 sphere (58,768 cells, 24^3, FP32)      5.80 -> 4.38 ms
-//   octree, 40 % refined (30,400 cells, 24^3)     5.76 -> 3.56 ms
+//   Mach-2 sphere (58,768 cells, 24^3, FP32)      5.80 -> 4.38 ms, 4.17 in
+//                                                 runs of 32 cells per XCD
+//   octree, 40 % refined (30,400 cells, 24^3)     5.76 -> 3.56 ms, 3.50
 //   the same in FP64 (10,427 cells)               3.40 -> 2.13 ms
 // (with them the median instruction in minmod, 8 % where no cell has a jump).
 // Measured and not kept: the same code for every cell at 576 and at 896 threads

@@ -49,3 +49,20 @@ def test_default_shape_is_one_plain_launch_bitwise(shape, nv, precision):
     else:
         assert np.array_equal(fa, fb)
         assert np.array_equal(ma, mb)
+
+
+def test_batch_of_fp64_24_is_the_one_launch_shape_bitwise():
+    """a batch has no pair of launches: its default shape there, set on a
+    solver, gives the batch's step bitwise; the pair is listed and set too"""
+    f = balanced(I.random_forest(9, (2, 2, 2), 3, 0.25, WALLS))
+    a, b = _solver(f, 24, D.PREC_FP64), _solver(f, 24, D.PREC_FP64)
+    assert b.get_shape()[:2] == (192, 21) and (192, 21) in b.shapes()
+    D.Batch([a], cfl=0.5).step(3)
+    b.set_shape(576, 30, 32, 1)
+    b.step(3, cfl=0.5)
+    b.set_shape(192, 21, 32, 1)
+    assert np.array_equal(a.f_canonical().cpu().numpy(), b.f_canonical().cpu().numpy())
+    assert np.array_equal(a.mom.cpu().numpy(), b.mom.cpu().numpy())
+    c = _solver(f, 24, D.PREC_FP32)
+    with pytest.raises(RuntimeError):
+        c.set_shape(192, 21, 32, 1)
