@@ -824,64 +824,80 @@ __device__ __forceinline__ void sep_flux(const double *R, int b, int hs, double 
 // the transport overwrites f.
 struct HybHook {
     HybArgs h;
-    // moments of the values leaving through face FACE (its axis and side
-    // compile-time constants, so the octants it selects are static)
+    // moments of the values leaving through face FACE of cell c (FACE < 0:
+    // face `face`, uniform).  Up to three rounds a thread one code serves the
+    // six faces and picks the octants by selects: with a copy per face the
+    // cells next to fluid ones spent their time fetching instructions (hybrid
+    // channel, 26,100 cells x 12^3 nodes FP32: 233 -> 177 us with the sensor;
+    // 262,144 cells x 8^3: 597 -> 540).  At nine rounds (24^3 FP32) the selects
+    // cost more: 719 us with copies, 775 without.
     template <int FACE, typename F, int NH, int T>
-    __device__ __forceinline__ void face_flux(const StepArgs &a, int64_t c, const Regs<F, NH, T> &fo,
+    __device__ __forceinline__ void face_flux(const StepArgs &a, int64_t c, int face, const Regs<F, NH, T> &fo,
                                               double *red) const {
         using L = Lane<NH, T>;
         constexpr int S = L::S;
-        constexpr int b = FACE >> 1, side = FACE & 1;
+        const int f = FACE < 0 ? face : FACE, b = f >> 1, side = f & 1;
         const L ln;
         // For a round the four leaving octants share |xi| and the sign along
         // b; only the signs along the other two axes (p, r) change.  So the
         // five moments need three sums of the stored values, formed in the
         // storage precision and widened once: S (all four), Sp and Sr (signed
         // by the sign along p and along r).
-        constexpr int p = b == 0 ? 1 : 0, r = b == 2 ? 1 : 2;
+        const int p = b == 0 ? 1 : 0, r = b == 2 ? 1 : 2;
         const double sg = side ? 1.0 : -1.0;
-        double v[5] = {0, 0, 0, 0, 0};
+        double v[5] = {0, 0, 0, 0, 0};  // density, along b, p, r, energy
 #pragma unroll
         for (int q = 0; q < S; ++q) {
             if (!ln.ok(q)) continue;
             F s0 = F(0), sp = F(0), sr = F(0);
 #pragma unroll
             for (int o = 0; o < 8; ++o) {
-                const int sgn[3] = {o >> 2, (o >> 1) & 1, o & 1};
-                if (sgn[b] != side) continue;  // not leaving through FACE
-                const F x = fo[o][q];
+                const bool leaves = ((o >> (2 - b)) & 1) == side;
+                if (FACE >= 0 && !leaves) continue;
+                const F x = leaves ? fo[o][q] : F(0);
                 s0 += x;
-                sp += sgn[p] ? x : -x;
-                sr += sgn[r] ? x : -x;
+                sp += (o >> (2 - p)) & 1 ? x : -x;
+                sr += (o >> (2 - r)) & 1 ? x : -x;
             }
             int a3[3];
             ln.axes(q, a3[0], a3[1], a3[2]);
-            const double ab[3] = {(a3[0] + 0.5) * a.g.dv[0], (a3[1] + 0.5) * a.g.dv[1], (a3[2] + 0.5) * a.g.dv[2]};
+            const double ax = (a3[0] + 0.5) * a.g.dv[0], ay = (a3[1] + 0.5) * a.g.dv[1],
+                         az = (a3[2] + 0.5) * a.g.dv[2];
             const double S0 = double(s0), Sp = double(sp), Sr = double(sr);
-            const double xb = sg * ab[b];  // xi . e_b of the leaving values
+            const double xb = sg * (b == 0 ? ax : b == 1 ? ay : az);  // xi . e_b of the leaving values
             v[0] += xb * S0;
-            v[1 + b] += xb * xb * S0;
-            v[1 + p] += xb * ab[p] * Sp;
-            v[1 + r] += xb * ab[r] * Sr;
-            v[4] += 0.5 * xb * ((ab[0] * ab[0] + ab[1] * ab[1]) + ab[2] * ab[2]) * S0;
+            v[1] += xb * xb * S0;
+            v[2] += xb * (b == 0 ? ay : ax) * Sp;
+            v[3] += xb * (b == 2 ? ay : az) * Sr;
+            v[4] += 0.5 * xb * ((ax * ax + ay * ay) + az * az) * S0;
         }
         block_sum<T, 5>(v, red);
-        if (threadIdx.x == 0)
-            for (int x = 0; x < 5; ++x) h.face[(c * 6 + FACE) * 5 + x] = a.g.w * v[x];
+        if (threadIdx.x == 0) {
+            double *out = h.face + (c * 6 + f) * 5;
+            out[0] = a.g.w * v[0];
+            out[1 + b] = a.g.w * v[1];
+            out[1 + p] = a.g.w * v[2];
+            out[1 + r] = a.g.w * v[3];
+            out[4] = a.g.w * v[4];
+        }
     }
     template <typename F, int NH, int T>
     __device__ __forceinline__ void apply(const StepArgs &a, int64_t c, const Regs<F, NH, T> &fo, double *red) const {
-        uint32_t faces = h.rows[c] >> 1;  // written by k_fluid_state
+        const uint32_t faces = h.rows[c] >> 1;  // written by k_fluid_state
 #pragma nounroll
         for (int f = 0; f < 6; ++f) {
             if (!((faces >> f) & 1)) continue;
-            switch (f) {
-            case 0: face_flux<0, F, NH, T>(a, c, fo, red); break;
-            case 1: face_flux<1, F, NH, T>(a, c, fo, red); break;
-            case 2: face_flux<2, F, NH, T>(a, c, fo, red); break;
-            case 3: face_flux<3, F, NH, T>(a, c, fo, red); break;
-            case 4: face_flux<4, F, NH, T>(a, c, fo, red); break;
-            default: face_flux<5, F, NH, T>(a, c, fo, red); break;
+            if constexpr (Lane<NH, T>::S <= 3) {
+                face_flux<-1, F, NH, T>(a, c, f, fo, red);
+            } else {
+                switch (f) {
+                case 0: face_flux<0, F, NH, T>(a, c, f, fo, red); break;
+                case 1: face_flux<1, F, NH, T>(a, c, f, fo, red); break;
+                case 2: face_flux<2, F, NH, T>(a, c, f, fo, red); break;
+                case 3: face_flux<3, F, NH, T>(a, c, f, fo, red); break;
+                case 4: face_flux<4, F, NH, T>(a, c, f, fo, red); break;
+                default: face_flux<5, F, NH, T>(a, c, f, fo, red); break;
+                }
             }
         }
     }
@@ -1058,7 +1074,16 @@ hipError_t hybrid_dispatch(const StepArgs &a, const HybArgs &h, hipStream_t st) 
         DVM_HYB(4, 64, 5, 0)
         DVM_HYB(6, 256, 6, 0)
         DVM_HYB(8, 256, 5, 0)
-        DVM_HYB(12, 192, 3, 1)
+    case 12:
+        // FP64 rows do not fit the registers of 192 threads at three waves per
+        // SIMD (394 spilled): the plain step's wide shape.  Channel, 8,000
+        // cells: 854 -> 576 us with the sensor (726 at five waves, 134 spilled).
+        if constexpr (std::is_same<F, double>::value) {
+            switch (a.g.nh) { DVM_HYB(12, 576, 3, 0) }
+        } else {
+            switch (a.g.nh) { DVM_HYB(12, 192, 3, 1) }
+        }
+        break;
     default: return hipErrorInvalidValue;
     }
 #undef DVM_HYB
