@@ -30,7 +30,6 @@ struct StepArgs {
     double dt;
     double h0;
     double dt_h0;            // dt / h0
-    double dt_tau;           // dt / tau_or_kn
     VelGrid g;
     int collision;           // DVM_COLL_*
     int tau_mode;            // DVM_TAU_*

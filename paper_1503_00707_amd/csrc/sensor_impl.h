@@ -160,7 +160,7 @@ __global__ __launch_bounds__(T) void k_labels(const F *f, float *r, VelGrid g) {
     const double rho = w * m[0];
     const double u[3] = {w * m[1] / rho, w * m[2] / rho, w * m[3] / rho};
     const double Tt = (2.0 * w * m[4] / rho - (u[0] * u[0] + u[1] * u[1] + u[2] * u[2])) / 3.0;
-    maxwell_tables<F, NH, T>(sm.mx, rho, u, Tt, rsqrt_f64(Tt), 1.0, g);
+    maxwell_tables<F, NH, T>(sm.mx, rho, u, Tt, 1.0, g);
     double s2[2] = {0.0, 0.0};
 #pragma unroll
     for (int q = 0; q < S; ++q) {
@@ -687,16 +687,16 @@ __global__ __launch_bounds__(64) void k_fluid_state(StepArgs a, HybArgs h) {
         h.rows[c] = uint8_t(((m == 0 && any_kin) || (m == 1 && pm == 0)) | (m == 1 ? fluid_faces << 1 : 0));
         h.prev[c] = uint8_t(m);
     }
-    const double rho = U[0], ir = rcp_f64(rho);
-    const double u[3] = {U[1] * ir, U[2] * ir, U[3] * ir};
-    const double Tt = (2.0 * U[4] * ir - ((u[0] * u[0] + u[1] * u[1]) + u[2] * u[2])) * (1.0 / 3.0);
+    const double rho = U[0];
+    const double u[3] = {U[1] / rho, U[2] / rho, U[3] / rho};
+    const double Tt = (2.0 * U[4] / rho - ((u[0] * u[0] + u[1] * u[1]) + u[2] * u[2])) / 3.0;
     bool act = cr < n && !m;
     if (act && (!(rho > 0.0) || !(Tt > 0.0))) {
         if (j == 0) *a.flag = 1;
         act = false;
     }
     if (!__any(act)) return;
-    const double isT = rsqrt_f64(Tt);
+    const double sT = sqrt(Tt);
     const int nh = a.g.nh, N = 2 * nh;
     double S[15], ck[3][2], gk[3][2];
 #pragma unroll
@@ -705,7 +705,7 @@ __global__ __launch_bounds__(64) void k_fluid_state(StepArgs a, HybArgs h) {
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
             const int k = j + 16 * s;
-            ck[b][s] = ((double(k - nh) + 0.5) * a.g.dv[b] - u[b]) * isT;
+            ck[b][s] = ((double(k - nh) + 0.5) * a.g.dv[b] - u[b]) / sT;
             gk[b][s] = 0.0;
             if (s == 0 || N > 16) gk[b][s] = k < N ? exp(-0.5 * ck[b][s] * ck[b][s]) : 0.0;
             double t = gk[b][s];
@@ -718,7 +718,8 @@ __global__ __launch_bounds__(64) void k_fluid_state(StepArgs a, HybArgs h) {
 #pragma unroll
         for (int q = 0; q < 5; ++q) S[5 * b + q] = row_sum(p[q]) * a.g.dv[b];
     }
-    const double n32 = 15.749609945722419 * Tt * (Tt * isT);  // (2 pi T)^(3/2)
+    const double x2 = 6.283185307179586476925286766559 * Tt;
+    const double C = rho / (x2 * sqrt(x2)), n32 = rho / C;
     double A[5][6], d[5];
 #pragma unroll
     for (int i = 0; i < 5; ++i)
@@ -728,18 +729,16 @@ __global__ __launch_bounds__(64) void k_fluid_state(StepArgs a, HybArgs h) {
     for (int i = 0; i < 5; ++i) A[i][5] = (i == 0 ? 1.0 : i == 4 ? 3.0 : 0.0) * n32 - A[i][0];
 #pragma unroll
     for (int k = 0; k < 5; ++k) {
-        const double pv = rcp_f64(A[k][k]);
 #pragma unroll
         for (int i = 0; i < 5; ++i) {
             if (i == k) continue;
-            const double t = A[i][k] * pv;
+            const double t = A[i][k] / A[k][k];
 #pragma unroll
             for (int l = k + 1; l < 6; ++l) A[i][l] -= t * A[k][l];
         }
     }
 #pragma unroll
-    for (int i = 0; i < 5; ++i) d[i] = A[i][5] * rcp_f64(A[i][i]);
-    const double C = rho * rcp_f64(n32);
+    for (int i = 0; i < 5; ++i) d[i] = A[i][5] / A[i][i];
 #pragma unroll
     for (int b = 0; b < 3; ++b)
 #pragma unroll
@@ -788,7 +787,7 @@ __global__ __launch_bounds__(T) void k_hybrid_rows(StepArgs a, HybArgs h) {
         if (threadIdx.x == 0) *a.flag = 1;
         return;
     }
-    maxwell_tables<F, NH, T>(sm, rho, u, Tt, rsqrt_f64(Tt), 1.0, a.g);
+    maxwell_tables<F, NH, T>(sm, rho, u, Tt, 1.0, a.g);
     F zero[8][Lane<NH, T>::S];
     for (int q = 0; q < Lane<NH, T>::S; ++q)
         for (int o = 0; o < 8; ++o) zero[o][q] = F(0);

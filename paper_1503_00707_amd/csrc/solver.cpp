@@ -93,7 +93,6 @@ StepArgs dvm::solver_step_args(const dvm_solver *s, double dt) {
     a.dt = dt;
     a.h0 = s->m->h0;
     a.dt_h0 = dt / s->m->h0;
-    a.dt_tau = dt / s->p.tau_or_kn;
     a.g = s->g;
     // the Korobov collision runs as its own kernel after a transport-only step
     a.collision = s->korobov() ? DVM_COLL_OFF : s->p.collision;

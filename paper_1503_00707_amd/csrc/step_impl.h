@@ -90,20 +90,6 @@ __device__ inline double wave_sum(double v) {
     return (readlane_f64(v, 0) + readlane_f64(v, 16)) + (readlane_f64(v, 32) + readlane_f64(v, 48));
 }
 
-// 1/x and 1/sqrt(x) to an ulp or two for normal x: the hardware's estimates
-// refined by two Newton steps, without the exponent scaling of a full division
-// (a third of its instructions; a cell's fixed work has some twenty of them).
-__device__ __forceinline__ double rcp_f64(double x) {
-    double y = __builtin_amdgcn_rcp(x);
-    y = __builtin_fma(y, __builtin_fma(-x, y, 1.0), y);
-    return __builtin_fma(y, __builtin_fma(-x, y, 1.0), y);
-}
-__device__ __forceinline__ double rsqrt_f64(double x) {
-    double y = __builtin_amdgcn_rsq(x);
-    y = __builtin_fma(0.5 * y, __builtin_fma(-x * y, y, 1.0), y);
-    return __builtin_fma(0.5 * y, __builtin_fma(-x * y, y, 1.0), y);
-}
-
 // Sum over a row of 16 lanes; every lane of the row receives it.
 __device__ __forceinline__ double row_sum(double v) {
     v += dpp_f64<0xb1>(v);
@@ -339,13 +325,15 @@ __device__ inline double gram_entry(int i, int j, const double *X, const double 
 // On the small grids this and the moments are most of a step's arithmetic: up
 // to 16 nodes an axis take one row of 16 lanes, and where the workgroup has
 // fewer waves than axes the three share the first wave (one after another
-// before: with the divisions 243,200 cells x 8^3 nodes FP32 took 657 us, now
-// 342; 16^3 cells x 8^3 nodes FP64 28.0 -> 19.7 us with the global sums; 380
-// and 22.7 before the cells went over the XCDs in runs).
-// isT = 1 / sqrt(Tt).
+// before: 243,200 cells x 8^3 nodes FP32 657 us, now 401; 16^3 cells x 8^3
+// nodes FP64 28.0 -> 20.6 us with the global sums; both with the cells over
+// the XCDs in runs).  The quotients and roots are full divisions: reciprocals
+// by two Newton steps took 340 and 19.4 us but left the FP64 step 1.3 to 1.8
+// times as far from the exact one (2.1e-16 -> 3.9e-16 of the largest value)
+// and densities without a normal reciprocal as NaN.
 template <typename F, int NH, int T>
 __device__ __forceinline__ void maxwell_solve(MaxwellSmem<F, NH> &sm, double rho, const double u[3], double Tt,
-                                              double isT, const VelGrid &g) {
+                                              const VelGrid &g) {
     constexpr int N = 2 * NH;
     constexpr int NW = (T + 63) / 64;
     static_assert(N <= 64, "one wave per axis");
@@ -357,7 +345,7 @@ __device__ __forceinline__ void maxwell_solve(MaxwellSmem<F, NH> &sm, double rho
             const double dv = b == 0 ? g.dv[0] : b == 1 ? g.dv[1] : g.dv[2];
             const double ub = b == 0 ? u[0] : b == 1 ? u[1] : u[2];
             double p[5];
-            const double ck = ((double(k - NH) + 0.5) * dv - ub) * isT;
+            const double ck = ((double(k - NH) + 0.5) * dv - ub) / sqrt(Tt);
             p[0] = exp(-0.5 * ck * ck);
             if (b < 3 && k < N) {
                 sm.g[b][k] = p[0];
@@ -377,7 +365,7 @@ __device__ __forceinline__ void maxwell_solve(MaxwellSmem<F, NH> &sm, double rho
             double gk = 0.0, ck = 0.0;
             if (lane < N) {
                 const double xi = (double(lane - NH) + 0.5) * g.dv[b];
-                ck = (xi - u[b]) * isT;
+                ck = (xi - u[b]) / sqrt(Tt);
                 gk = exp(-0.5 * ck * ck);
                 sm.g[b][lane] = gk;
                 sm.c[b][lane] = ck;
@@ -396,27 +384,28 @@ __device__ __forceinline__ void maxwell_solve(MaxwellSmem<F, NH> &sm, double rho
     if (wid == 0) {
         const int i = lane / 6, j = lane % 6;
         const bool el = lane < 30;
-        const double n32 = 15.749609945722419 * Tt * (Tt * isT);  // (2 pi T)^(3/2)
+        const double x2 = 6.283185307179586476925286766559 * Tt;
+        const double C = rho / (x2 * sqrt(x2));
         // lane 6i + j holds A[i][j]; each elimination step reads the pivot
         // row and column from the lanes that hold them (no LDS round trip)
         double x = 0.0;
         if (el) {
             if (j < 5) x = gram_entry(i, j, &sm.S[0], &sm.S[5], &sm.S[10]);
             else {
-                const double t = (i == 0 ? 1.0 : i == 4 ? 3.0 : 0.0) * n32;
+                const double t = (i == 0 ? 1.0 : i == 4 ? 3.0 : 0.0) * (rho / C);
                 x = t - gram_entry(i, 0, &sm.S[0], &sm.S[5], &sm.S[10]);
             }
         }
 #pragma unroll
         for (int k = 0; k < 5; ++k) {
-            const double r = rcp_f64(readlane_f64(x, 7 * k));
+            const double akk = readlane_f64(x, 7 * k);
             const double aik = shfl_f64(x, 6 * i + k);
             const double akj = shfl_f64(x, 6 * k + j);
-            if (el && i != k) x = x - aik * r * akj;
+            if (el && i != k) x = x - aik / akk * akj;
         }
         const double diag = shfl_f64(x, 7 * lane), rhs = shfl_f64(x, 6 * lane + 5);
-        if (lane < 5) sm.d[lane] = rhs * rcp_f64(diag);
-        if (lane == 0) sm.C = rho * rcp_f64(n32);
+        if (lane < 5) sm.d[lane] = rhs / diag;
+        if (lane == 0) sm.C = C;
     }
     __syncthreads();
 }
@@ -429,9 +418,10 @@ __device__ void maxwell_fill(MaxwellSmem<F, NH> &sm, double mfac) {
     constexpr int NW = (T + 63) / 64;
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     const auto fill = [&](int b, int k) {
-        const double cc = sm.c[b][k], db = sm.d[1 + b] * cc + sm.d[4] * cc * cc;
+        const double cc = sm.c[b][k];
         sm.tab[b][k][0] = F(b == 0 ? sm.g[b][k] * sm.C * mfac : sm.g[b][k]);
-        sm.tab[b][k][1] = F(b == 0 ? 1.0 + sm.d[0] + db : db);
+        sm.tab[b][k][1] = F(b == 0 ? 1.0 + sm.d[0] + sm.d[1] * cc + sm.d[4] * cc * cc
+                                   : sm.d[1 + b] * cc + sm.d[4] * cc * cc);
     };
     if constexpr (N <= 16) {
         const int b = NW >= 3 ? (lane < 16 ? wid : 3) : wid == 0 ? lane >> 4 : 3;
@@ -445,8 +435,8 @@ __device__ void maxwell_fill(MaxwellSmem<F, NH> &sm, double mfac) {
 
 template <typename F, int NH, int T>
 __device__ __forceinline__ void maxwell_tables(MaxwellSmem<F, NH> &sm, double rho, const double u[3], double Tt,
-                                               double isT, double mfac, const VelGrid &g) {
-    maxwell_solve<F, NH, T>(sm, rho, u, Tt, isT, g);
+                                               double mfac, const VelGrid &g) {
+    maxwell_solve<F, NH, T>(sm, rho, u, Tt, g);
     maxwell_fill<F, NH, T>(sm, mfac);
 }
 
@@ -1332,10 +1322,10 @@ __device__ __forceinline__ void step_cell(const StepArgs &a, int64_t c, StepSmem
     block_sum<T, 5>(m, sm.red);
 
     const double w = a.g.w;
-    const double rho = w * m[0], ir = rcp_f64(rho);
-    const double u[3] = {w * m[1] * ir, w * m[2] * ir, w * m[3] * ir};
+    const double rho = w * m[0];
+    const double u[3] = {w * m[1] / rho, w * m[2] / rho, w * m[3] / rho};
     const double E = w * m[4];
-    const double Tt = (2.0 * E * ir - (u[0] * u[0] + u[1] * u[1] + u[2] * u[2])) * (1.0 / 3.0);
+    const double Tt = (2.0 * E / rho - (u[0] * u[0] + u[1] * u[1] + u[2] * u[2])) / 3.0;
     const bool bad = !(rho > 0.0) || !(Tt > 0.0);
     if (tid == 0) {
         const int64_t n = a.n_cells;
@@ -1356,8 +1346,8 @@ __device__ __forceinline__ void step_cell(const StepArgs &a, int64_t c, StepSmem
         }
         return;
     }
-    const double isT = rsqrt_f64(Tt);
-    const double x = a.tau_mode == DVM_TAU_HS ? a.dt_tau * (rho * (Tt * isT)) : a.dt_tau;  // dt / tau
+    const double tau = a.tau_mode == DVM_TAU_HS ? a.tau_or_kn / (rho * sqrt(Tt)) : a.tau_or_kn;
+    const double x = a.dt / tau;
     // explicit Euler: f + x (Mt - f); exponential: Mt + e^{-x} (f - Mt), e^{-x}
     // by itself: 1 - mfac has lost its digits where x is large, and with them
     // every value far above its Maxwellian (relative error of 1 - mfac: 1e-13
@@ -1365,7 +1355,7 @@ __device__ __forceinline__ void step_cell(const StepArgs &a, int64_t c, StepSmem
     const bool euler = a.collision == DVM_COLL_EULER;
     const double mfac = euler ? x : -expm1(-x);
     const double e = euler ? 1.0 - x : exp(-x);
-    maxwell_tables<F, NH, T>(sm.mx, rho, u, Tt, isT, mfac, a.g);
+    maxwell_tables<F, NH, T>(sm.mx, rho, u, Tt, mfac, a.g);
     relax_store<F, NH, T, NT>(sm.mx, fo, F(e), out);
 }
 
@@ -1463,7 +1453,7 @@ __global__ __launch_bounds__(T) void k_init(InitArgs a) {
         for (int b = 0; b < 3; ++b) a.mom[(1 + b) * a.n + c] = rho * u[b];
         a.mom[4 * a.n + c] = 0.5 * rho * (u[0] * u[0] + u[1] * u[1] + u[2] * u[2]) + 1.5 * rho * Tt;
     }
-    maxwell_tables<F, NH, T>(sm, rho, u, Tt, rsqrt_f64(Tt), 1.0, a.g);
+    maxwell_tables<F, NH, T>(sm, rho, u, Tt, 1.0, a.g);
     F zero[8][S];
 #pragma unroll
     for (int q = 0; q < S; ++q)
