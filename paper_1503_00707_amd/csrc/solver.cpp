@@ -227,7 +227,12 @@ int dvm_create_solver(const dvm_mesh *m, const dvm_params *p, dvm_solver **out) 
             if (irregular == (pass == 1)) s->sel_host.push_back(uint32_t(c));
             if (pass == 0 && !irregular) ++s->n_reg;
         }
+    // the second launch's shape: one with a full kernel, which the pair has not
     s->cfg_irr = s->cfg;
+    if (two_shapes(s, s->cfg)) {
+        s->cfg_irr.threads = kOneShape.threads;
+        s->cfg_irr.wpe = kOneShape.wpe;
+    }
     s->ws_bytes = o;
     *out = s;
     return DVM_OK;
