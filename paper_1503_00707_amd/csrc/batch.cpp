@@ -214,7 +214,7 @@ int dvm_batch_create(dvm_solver *const *solvers, int32_t n, double cfl, dvm_batc
             it = b->groups.end() - 1;
             it->nh = solvers[i]->nh;
             it->cfg = solvers[i]->cfg;
-            if (has_two_shapes(solvers[i]) && it->cfg.threads == kTwoShapes.threads && it->cfg.wpe == kTwoShapes.wpe) {
+            if (has_two_shapes(solvers[i]) && is_two_shapes(it->cfg.threads, it->cfg.wpe)) {
                 it->cfg.threads = kOneShape.threads;  // one launch over all cells of the group
                 it->cfg.wpe = kOneShape.wpe;
             }

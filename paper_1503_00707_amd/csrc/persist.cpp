@@ -116,7 +116,7 @@ hipError_t trial_step(const dvm_solver *s, const StepConfig &cfg, double dt, hip
     while ((1 << (a.xcd_log2 + 1)) <= cfg.xcd_group) ++a.xcd_log2;
     a.f_in = s->f[s->cur];
     a.f_out = s->f[s->cur ^ 1];
-    return enqueue_step(s, a, cfg, st);
+    return launch_shape(s, a, cfg, st);
 }
 
 }  // namespace
@@ -255,7 +255,10 @@ int dvm_tune(dvm_solver *s, const char *cache_path, int32_t reps, int32_t *from_
     const int groups[5] = {1, 8, 32, 64, 512};
     double best = 1e300;
     StepConfig best_cfg = s->cfg;
-    for (int k = 0; k < nk && rc == DVM_OK; ++k)
+    for (int k = 0; k < nk && rc == DVM_OK; ++k) {
+        // without regular cells the pair is its second launch alone, a shape of
+        // the list: its time would stand for both in the cache
+        if (has_two_shapes(s) && is_two_shapes(thr[k], wpe[k]) && s->n_reg == 0) continue;
         for (int xg : groups)
             for (int nt = 0; nt < 2 && rc == DVM_OK; ++nt) {
                 const StepConfig cfg{thr[k], xg, nt, wpe[k], 0};
@@ -275,6 +278,7 @@ int dvm_tune(dvm_solver *s, const char *cache_path, int32_t reps, int32_t *from_
                     best_cfg = cfg;
                 }
             }
+    }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (rc) return rc;

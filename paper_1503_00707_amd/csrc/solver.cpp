@@ -13,13 +13,6 @@
 using namespace dvm;
 
 namespace {
-// two launches (reduced kernel over the regular cells, full kernel over the
-// rest) instead of one: first order, kernels compiled
-bool use_split(const dvm_solver *s, const StepConfig &cfg) {
-    return s->split && !s->muscl && s->n_reg > 0 && have_regular_kernel(s->nh, cfg.threads, cfg.wpe) &&
-           have_kernel(s->nh, s->cfg_irr.threads, s->cfg_irr.wpe);
-}
-
 // The FP64 default at 24^3 nodes, shape (192, 21): the regular cells with 192
 // threads at two waves per SIMD in one launch and the others with 576 at five
 // in a second.  Regular cells hold three
@@ -29,7 +22,34 @@ bool use_split(const dvm_solver *s, const StepConfig &cfg) {
 // threads 2,555 us, at 192 threads 2,663, two launches 2,317; 570 cells: 71,
 // 128, 71).  FP32 keeps one launch: 420,251 cells 12.5 ms against 14.0.
 bool two_shapes(const dvm_solver *s, const StepConfig &cfg) {
-    return has_two_shapes(s) && cfg.threads == kTwoShapes.threads && cfg.wpe == kTwoShapes.wpe;
+    return has_two_shapes(s) && is_two_shapes(cfg.threads, cfg.wpe);
+}
+
+// two launches (reduced kernel over the regular cells, full kernel over the
+// rest) instead of one: first order, kernels compiled
+bool use_split(const dvm_solver *s, const StepConfig &cfg) {
+    return s->split && !s->muscl && s->n_reg > 0 &&
+           (two_shapes(s, cfg) || have_regular_kernel(s->nh, cfg.threads, cfg.wpe)) &&
+           have_kernel(s->nh, s->cfg_irr.threads, s->cfg_irr.wpe);
+}
+
+// the regular cells in shape cfg's reduced kernel, the others in shape irr
+hipError_t launch_pair(const dvm_solver *s, const StepArgs &a, const StepConfig &cfg, ShapeId irr, hipStream_t st) {
+    StepConfig c = cfg;  // stores and grouping as chosen; each launch its own shape
+    StepArgs part = a;
+    if (s->n_reg > 0) {
+        c.regular = 1;
+        part.sel = s->sel();
+        part.n_sel = s->n_reg;
+        hipError_t e = launch_step(s->fp64, part, c, st);
+        if (e != hipSuccess || s->n == s->n_reg) return e;
+    }
+    c.regular = 0;
+    c.threads = irr.threads;
+    c.wpe = irr.wpe;
+    part.sel = s->sel() + s->n_reg;
+    part.n_sel = s->n - s->n_reg;
+    return launch_step(s->fp64, part, c, st);
 }
 }  // namespace
 
@@ -52,33 +72,9 @@ void dvm::default_grouping(StepConfig &c, int nh, int64_t n, double state_bytes)
     c.nt_store = state_bytes > 128.0 * (1 << 20);
 }
 
-hipError_t dvm::enqueue_step(const dvm_solver *s, const StepArgs &a, const StepConfig &cfg, hipStream_t st) {
-    StepConfig reg = cfg, irr = cfg;  // stores and grouping as chosen; its own shapes
-    if (use_split(s, cfg)) {
-        irr.threads = s->cfg_irr.threads;
-        irr.wpe = s->cfg_irr.wpe;
-    } else if (two_shapes(s, cfg)) {
-        irr.threads = 576;
-        irr.wpe = 51;
-        // no regular cell, or dvm_tune_split has been called: its two settings
-        // are the same step bitwise, in one launch (no reduced kernel at 576)
-        if (s->n_reg == 0 || s->split_set) {
-            irr.wpe = kOneShape.wpe;
-            return launch_step(s->fp64, a, irr, st);
-        }
-    } else {
-        return launch_step(s->fp64, a, cfg, st);
-    }
-    reg.regular = 1;
-    irr.regular = 0;
-    StepArgs part = a;
-    part.sel = s->sel();
-    part.n_sel = s->n_reg;
-    hipError_t e = launch_step(s->fp64, part, reg, st);
-    if (e != hipSuccess || s->n == s->n_reg) return e;
-    part.sel = s->sel() + s->n_reg;
-    part.n_sel = s->n - s->n_reg;
-    return launch_step(s->fp64, part, irr, st);
+hipError_t dvm::launch_shape(const dvm_solver *s, const StepArgs &a, const StepConfig &cfg, hipStream_t st) {
+    if (two_shapes(s, cfg)) return launch_pair(s, a, cfg, ShapeId{576, 51}, st);
+    return launch_step(s->fp64, a, cfg, st);
 }
 
 StepArgs dvm::solver_step_args(const dvm_solver *s, double dt) {
@@ -379,7 +375,8 @@ int dvm_step(dvm_solver *s, int32_t n_steps, double dt, double cfl, void *stream
     for (int it = 0; it < n_steps; ++it) {
         a.f_in = s->f[s->cur];
         a.f_out = s->f[s->cur ^ 1];
-        e = enqueue_step(s, a, s->cfg, st);
+        e = use_split(s, s->cfg) ? launch_pair(s, a, s->cfg, ShapeId{s->cfg_irr.threads, s->cfg_irr.wpe}, st)
+                                 : launch_shape(s, a, s->cfg, st);
         if (e != hipSuccess) return hip_fail(e, "step");
         if (s->korobov()) {
             KorArgs k{};
@@ -536,7 +533,6 @@ int dvm_tune_split(dvm_solver *s, int32_t enable, int32_t threads_irr, int32_t w
         s->cfg_irr.wpe = wpe_irr;
     }
     s->split = enable != 0;
-    s->split_set = true;
     return DVM_OK;
 }
 

@@ -57,9 +57,9 @@ struct dvm_solver {
     // first order: optionally step the cells without FINER or
     // WALL faces ("regular") in a reduced kernel and the others in a second
     // launch (off by default: one launch takes the reduced code path per cell
-    // and keeps Morton locality between the two kinds; FP64 at 24^3 nodes
-    // takes two unless told otherwise)
-    bool split = false, split_set = false;  // split_set: dvm_tune_split has chosen
+    // and keeps Morton locality between the two kinds; the shape kTwoShapes is
+    // two launches whatever this says)
+    bool split = false;
     bool cfg_default = true;                // cfg as dvm_create set it
     int64_t n_reg = 0;             // regular cells: the first n_reg entries of the selection list
     size_t off_sel = 0;            // selection list [n] (regular cells, then the others; Morton order)
@@ -103,10 +103,11 @@ struct ShapeId {
 };
 constexpr ShapeId kTwoShapes{192, 21}, kOneShape{576, 30};
 inline bool has_two_shapes(const dvm_solver *s) { return s->fp64 && s->nh == 12 && !s->muscl; }
+inline bool is_two_shapes(int threads, int wpe) { return threads == kTwoShapes.threads && wpe == kTwoShapes.wpe; }
 // a shape that dvm_step takes
 inline bool have_shape(const dvm_solver *s, int threads, int wpe) {
     return have_kernel(s->nh, threads, wpe) ||
-           (has_two_shapes(s) && threads == kTwoShapes.threads && wpe == kTwoShapes.wpe);
+           (has_two_shapes(s) && is_two_shapes(threads, wpe));
 }
 // the shapes dvm_step takes (at most cap written); returns their number
 inline int list_shapes(const dvm_solver *s, int *threads, int *wpe, int cap) {
@@ -120,8 +121,8 @@ inline int list_shapes(const dvm_solver *s, int *threads, int *wpe, int cap) {
     }
     return n;
 }
-// one step of the solver with shape cfg, a complete: one launch or two
-hipError_t enqueue_step(const dvm_solver *s, const StepArgs &a, const StepConfig &cfg, hipStream_t st);
+// one step of the solver with shape cfg, a complete: one launch, the pair's two
+hipError_t launch_shape(const dvm_solver *s, const StepArgs &a, const StepConfig &cfg, hipStream_t st);
 // default runs of cells per XCD and kind of stores for n cells (state_bytes: one state buffer)
 void default_grouping(StepConfig &c, int nh, int64_t n, double state_bytes);
 double solver_max_speed_sum(const dvm_solver *s);

@@ -43,3 +43,43 @@ def test_split_of_192_threads_steps_the_other_cells_at_576(irr):
     assert not np.array_equal(narrow[1][:, ~reg], wide[1][:, ~reg])
     assert np.array_equal(both[0][reg], narrow[0][reg]) and np.array_equal(both[1][:, reg], narrow[1][:, reg])
     assert np.array_equal(both[0][~reg], wide[0][~reg]) and np.array_equal(both[1][:, ~reg], wide[1][:, ~reg])
+
+
+@pytest.mark.parametrize("mesh", ["walls", "jumps", "uniform"])
+def test_the_pair_is_one_launch_of_576_threads_bitwise(mesh):
+    """the default, whatever dvm_tune_split says, (576, 30) and a batch: one step"""
+    f = {"walls": _forest(), "jumps": balanced(I.random_forest(5, (2, 3, 2), 2, 0.3)),
+         "uniform": I.uniform_forest((3, 3, 3), 0)}[mesh]
+    f1, m1 = _stepped(f, (576, 30), steps=3)
+    for shape, split, irr in ((None, None, (0, 0)), (None, 0, (0, 0)), (None, 1, (0, 0)), (None, 1, (576, 71)),
+                              ((192, 21), None, (0, 0))):
+        f2, m2 = _stepped(f, shape, split, irr, steps=3)
+        assert np.array_equal(f1, f2) and np.array_equal(m1, m2), (shape, split, irr)
+    b = _solver(f, 24, D.PREC_FP64)
+    D.Batch([b], cfl=0.5).step(3)
+    assert np.array_equal(f1, b.f_canonical().cpu().numpy()) and np.array_equal(m1, b.mom.cpu().numpy())
+
+
+def test_a_second_launch_of_its_own_steps_the_other_cells_of_the_pair():
+    """dvm_tune_split(1, 192, 31) with the pair's shape: its regular cells as
+    ever, the others by 192 threads"""
+    f = _forest()
+    reg = _regular(f)
+    pair, narrow = _stepped(f, None), _stepped(f, (192, 31))
+    both = _stepped(f, None, 1, (192, 31))
+    assert np.array_equal(both[0][reg], pair[0][reg]) and np.array_equal(both[1][:, reg], pair[1][:, reg])
+    assert np.array_equal(both[0][~reg], narrow[0][~reg]) and np.array_equal(both[1][:, ~reg], narrow[1][:, ~reg])
+
+
+def test_without_regular_cells_the_pair_is_not_tuned():
+    """one cell between walls: its only launch is (576, 51), listed by itself"""
+    s = _solver(I.uniform_forest((1, 1, 1), 0, bc=(I.WALL,) * 6), 24, D.PREC_FP64)
+    for _ in range(3):
+        s.tune(reps=1)
+        assert s.get_shape()[:2] in s.shapes() and s.get_shape()[:2] != (192, 21)
+    t = _solver(I.uniform_forest((1, 1, 1), 0, bc=(I.WALL,) * 6), 24, D.PREC_FP64)
+    u = _solver(I.uniform_forest((1, 1, 1), 0, bc=(I.WALL,) * 6), 24, D.PREC_FP64)
+    u.set_shape(576, 30, 1, 0)
+    for x in (t, u):
+        x.step(2, cfl=0.5)
+    assert np.array_equal(t.f_canonical().cpu().numpy(), u.f_canonical().cpu().numpy())
