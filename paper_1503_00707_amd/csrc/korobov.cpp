@@ -123,8 +123,8 @@ void korobov_tables(int n, double vmax, int64_t p, int64_t a, std::vector<int32_
         sv[size_t(q)] = std::sin(ph);
     }
     auto cell_of = [&](double v) -> int {
-        const double t = std::floor((v - lo) / d);
-        return (t < 0.0 || t >= double(n)) ? -1 : int(t);
+        const double t = (v - lo) / d;
+        return t >= 0.0 && t < double(n) ? int(t) : -1;
     };
     for (int64_t i = 0; i < nv; ++i) {
         const int ix = int(i / (int64_t(n) * n)), iy = int((i / n) % n), iz = int(i % n);
@@ -184,29 +184,37 @@ inline int phase_lane(int phase, int t) {
 // their indices differ modulo 16.  Greedy: each lane takes, among the residues
 // (of x, of y) that no other lane has in this step, one it has most of.  Steps
 // beyond a lane's list get entries of weight 0 on free residues.
+// PAIR: the lists of partners, one row an entry (x = y).
+template <bool PAIR>
 void arrange(const std::vector<Entry> *lists, int64_t len, std::vector<Entry> *out) {
+    // entries left of residue r, with the smaller residue first among equals,
+    // as one number: (left << 4) + 15 - r
     struct Lane {
-        std::vector<Entry> e;     // sorted by residue pair
-        int32_t next[256], left[256], row[16];
-        uint32_t rows, cols[16];  // which residues of x, and of y under each, are left
+        std::vector<Entry> e;                          // sorted by residue pair
+        int64_t row[16], col[PAIR ? 1 : 256];          // of x; of y under each x
+        int32_t next[PAIR ? 16 : 256];
+        uint32_t rows, cols[16];                       // which of them are left
     };
+    constexpr size_t NB = PAIR ? 16 : 256;
+    const auto bucket = [](const Entry &e) { return PAIR ? size_t(e.x & 15) : size_t((e.x & 15) * 16 + (e.y & 15)); };
     std::vector<Lane> lane(16);
     for (int t = 0; t < 16; ++t) {
         Lane &z = lane[size_t(t)];
-        int32_t at[257] = {0};
-        const auto bucket = [](const Entry &e) { return size_t((e.x & 15) * 16 + (e.y & 15)); };
+        int32_t at[NB + 1] = {0};
         for (const Entry &e : lists[t]) at[bucket(e) + 1]++;
         z.rows = 0;
-        for (int q = 0; q < 16; ++q) {
-            z.row[q] = 0;
-            z.cols[q] = 0;
+        for (int r = 0; r < 16; ++r) {
+            z.row[r] = 15 - r;
+            z.cols[r] = 0;
         }
-        for (int q = 0; q < 256; ++q) {
-            z.left[q] = at[q + 1];
-            z.row[q >> 4] += at[q + 1];
-            if (at[q + 1]) {
-                z.rows |= 1u << (q >> 4);
-                z.cols[q >> 4] |= 1u << (q & 15);
+        for (size_t q = 0; q < NB; ++q) {
+            const size_t x = PAIR ? q : q >> 4;
+            const int64_t left = at[q + 1];
+            z.row[x] += left * 16;
+            if constexpr (!PAIR) z.col[q] = left * 16 + 15 - int64_t(q & 15);
+            if (left) {
+                z.rows |= 1u << x;
+                if (!PAIR) z.cols[x] |= 1u << (q & 15);
             }
             at[q + 1] += at[q];
             z.next[q] = at[q];
@@ -217,13 +225,10 @@ void arrange(const std::vector<Entry> *lists, int64_t len, std::vector<Entry> *o
         out[t].reserve(size_t(len));
     }
     // the residue of which a lane has most, among those in `of`
-    const auto most = [](uint32_t of, const int32_t *left) {
-        int best = -1;
-        for (; of; of &= of - 1) {
-            const int r = __builtin_ctz(of);
-            if (best < 0 || left[r] > left[best]) best = r;
-        }
-        return best;
+    const auto most = [](uint32_t of, const int64_t *key) {
+        int64_t best = -1;
+        for (; of; of &= of - 1) best = std::max(best, key[__builtin_ctz(of)]);
+        return best < 0 ? -1 : int(15 - (best & 15));
     };
     for (int64_t k = 0; k < len; ++k) {
         uint32_t ux = 0, uy = 0;
@@ -236,16 +241,17 @@ void arrange(const std::vector<Entry> *lists, int64_t len, std::vector<Entry> *o
                 for (uint32_t of = z.rows & ~ux; of && y < 0;) {
                     x = most(of, z.row);
                     of &= ~(1u << x);
-                    y = most(z.cols[x] & ~uy, z.left + 16 * x);
+                    y = PAIR ? x : most(z.cols[x] & ~uy, z.col + (PAIR ? 0 : 16 * x));
                 }
                 if (y < 0) {  // no pair is free: any that is left
                     x = __builtin_ctz(z.rows);
                     const uint32_t of = z.cols[x] & ~uy;
-                    y = __builtin_ctz(of ? of : z.cols[x]);
+                    y = PAIR ? x : __builtin_ctz(of ? of : z.cols[x]);
                 }
-                const int b = 16 * x + y;
-                if (--z.left[b] == 0) z.cols[x] &= ~(1u << y);
-                if (--z.row[x] == 0) z.rows &= ~(1u << x);
+                const int b = PAIR ? x : 16 * x + y;
+                if constexpr (!PAIR)
+                    if ((z.col[b] -= 16) < 16) z.cols[x] &= ~(1u << y);
+                if ((z.row[x] -= 16) < 16) z.rows &= ~(1u << x);
                 take = z.e[size_t(z.next[b]++)];
             } else {
                 take.x = uint16_t(ux == 0xffffu ? 0 : __builtin_ctz(~ux));
@@ -359,9 +365,9 @@ void korobov_plan(int nh, double vmax, const std::vector<int32_t> &J, const std:
                 }
             }
         }
-        arrange(list, len[g], put);
-        for (int t = 0; t < 16; ++t)
-            for (int64_t k = 0; k < len[g]; ++k) {
+        arrange<false>(list, len[g], put);
+        for (int64_t k = 0; k < len[g]; ++k)
+            for (int t = 0; t < 16; ++t) {
                 const Entry &e = put[t][size_t(k)];
                 gain[size_t(at[g]) + size_t(k * 64 + slot_of(t) % 64)] =
                     uint64_t(e.x) | (uint64_t(e.y) << 16) | (uint64_t(e.d2) << 32);
@@ -376,9 +382,9 @@ void korobov_plan(int nh, double vmax, const std::vector<int32_t> &J, const std:
                 list[t].push_back(Entry{r, r, dist2(i, j)});
             }
         }
-        arrange(list, p, put);
-        for (int t = 0; t < 16; ++t)
-            for (int64_t k = 0; k < p; ++k) {
+        arrange<true>(list, p, put);
+        for (int64_t k = 0; k < p; ++k)
+            for (int t = 0; t < 16; ++t) {
                 const Entry &e = put[t][size_t(k)];
                 pair[size_t(k * nv + slot_of(t))] = uint32_t(e.x) | (e.d2 << 16);
             }
