@@ -256,9 +256,9 @@ int dvm_tune(dvm_solver *s, const char *cache_path, int32_t reps, int32_t *from_
     double best = 1e300;
     StepConfig best_cfg = s->cfg;
     for (int k = 0; k < nk && rc == DVM_OK; ++k) {
-        // without regular cells the pair is its second launch alone, a shape of
-        // the list: its time would stand for both in the cache
-        if (has_two_shapes(s) && is_two_shapes(thr[k], wpe[k]) && s->n_reg == 0) continue;
+        // where the pair is one launch, of a shape that is listed too, its time
+        // would stand for a pair in the cache
+        if (has_two_shapes(s) && is_two_shapes(thr[k], wpe[k]) && !runs_as_pair(s)) continue;
         for (int xg : groups)
             for (int nt = 0; nt < 2 && rc == DVM_OK; ++nt) {
                 const StepConfig cfg{thr[k], xg, nt, wpe[k], 0};

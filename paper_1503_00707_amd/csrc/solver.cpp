@@ -15,12 +15,12 @@ using namespace dvm;
 namespace {
 // The FP64 default at 24^3 nodes, shape (192, 21): the regular cells with 192
 // threads at two waves per SIMD in one launch and the others with 576 at five
-// in a second.  Regular cells hold three
-// times the loads in flight per wave that way (27,000 of them: 1,962 -> 1,581
-// us); the correction pass over the four rows behind a FINER face wants the
-// wide workgroup (30,400 cells, 16 % with such faces: one launch at 576
-// threads 2,555 us, at 192 threads 2,663, two launches 2,317; 570 cells: 71,
-// 128, 71).  FP32 keeps one launch: 420,251 cells 12.5 ms against 14.0.
+// in a second.  Regular cells hold three times the loads in flight per wave
+// that way (27,000 of them: 1,962 -> 1,581 us); the correction pass over the
+// four rows behind a FINER face wants the wide workgroup (30,400 cells, 16 %
+// with such faces: one launch at 576 threads 2,555 us, at 192 threads 2,663,
+// two launches 2,317).  FP32 keeps one launch: 420,251 cells 12.5 ms against
+// 14.0.
 bool two_shapes(const dvm_solver *s, const StepConfig &cfg) {
     return has_two_shapes(s) && is_two_shapes(cfg.threads, cfg.wpe);
 }
@@ -33,17 +33,16 @@ bool use_split(const dvm_solver *s, const StepConfig &cfg) {
            have_kernel(s->nh, s->cfg_irr.threads, s->cfg_irr.wpe);
 }
 
-// the regular cells in shape cfg's reduced kernel, the others in shape irr
+// the regular cells (at least one) in shape cfg's reduced kernel, the others in
+// shape irr
 hipError_t launch_pair(const dvm_solver *s, const StepArgs &a, const StepConfig &cfg, ShapeId irr, hipStream_t st) {
     StepConfig c = cfg;  // stores and grouping as chosen; each launch its own shape
+    c.regular = 1;
     StepArgs part = a;
-    if (s->n_reg > 0) {
-        c.regular = 1;
-        part.sel = s->sel();
-        part.n_sel = s->n_reg;
-        hipError_t e = launch_step(s->fp64, part, c, st);
-        if (e != hipSuccess || s->n == s->n_reg) return e;
-    }
+    part.sel = s->sel();
+    part.n_sel = s->n_reg;
+    hipError_t e = launch_step(s->fp64, part, c, st);
+    if (e != hipSuccess || s->n == s->n_reg) return e;
     c.regular = 0;
     c.threads = irr.threads;
     c.wpe = irr.wpe;
@@ -72,9 +71,23 @@ void dvm::default_grouping(StepConfig &c, int nh, int64_t n, double state_bytes)
     c.nt_store = state_bytes > 128.0 * (1 << 20);
 }
 
+// On few cells the pair costs more than it gives: two launches one after the
+// other, neither of which fills the card (one launch at 576 threads / the pair,
+// us; 27 cells between walls 19 / 35, 209 cells with jumps 31.5 / 49.4, 581: 57
+// / 64, 1,057: 100 / 96, 1,452 between walls 112 / 121, 1,583: 147 / 142, 2,255:
+// 214 / 197).  Without other cells there is no second launch: 216 cells 20.0 /
+// 21.0, 343: 32.7 / 27.9.
+bool dvm::runs_as_pair(const dvm_solver *s) {
+    return s->n_reg > 0 && s->n > (s->n_reg == s->n ? 256 : 1536);
+}
+
 hipError_t dvm::launch_shape(const dvm_solver *s, const StepArgs &a, const StepConfig &cfg, hipStream_t st) {
-    if (two_shapes(s, cfg)) return launch_pair(s, a, cfg, ShapeId{576, 51}, st);
-    return launch_step(s->fp64, a, cfg, st);
+    if (!two_shapes(s, cfg)) return launch_step(s->fp64, a, cfg, st);
+    if (runs_as_pair(s)) return launch_pair(s, a, cfg, ShapeId{576, 51}, st);
+    StepConfig one = cfg;
+    one.threads = kOneShape.threads;
+    one.wpe = kOneShape.wpe;
+    return launch_step(s->fp64, a, one, st);
 }
 
 StepArgs dvm::solver_step_args(const dvm_solver *s, double dt) {

@@ -58,7 +58,7 @@ struct dvm_solver {
     // WALL faces ("regular") in a reduced kernel and the others in a second
     // launch (off by default: one launch takes the reduced code path per cell
     // and keeps Morton locality between the two kinds; the shape kTwoShapes is
-    // two launches whatever this says)
+    // two launches by itself)
     bool split = false;
     bool cfg_default = true;                // cfg as dvm_create set it
     int64_t n_reg = 0;             // regular cells: the first n_reg entries of the selection list
@@ -121,6 +121,8 @@ inline int list_shapes(const dvm_solver *s, int *threads, int *wpe, int cap) {
     }
     return n;
 }
+// whether the shape kTwoShapes is two launches on this mesh
+bool runs_as_pair(const dvm_solver *s);
 // one step of the solver with shape cfg, a complete: one launch, the pair's two
 hipError_t launch_shape(const dvm_solver *s, const StepArgs &a, const StepConfig &cfg, hipStream_t st);
 // default runs of cells per XCD and kind of stores for n cells (state_bytes: one state buffer)

@@ -83,3 +83,35 @@ def test_without_regular_cells_the_pair_is_not_tuned():
     for x in (t, u):
         x.step(2, cfl=0.5)
     assert np.array_equal(t.f_canonical().cpu().numpy(), u.f_canonical().cpu().numpy())
+
+
+@pytest.mark.parametrize("shape,frac", [((16, 4, 4), 0.0), ((257, 1, 1), 0.0), ((8, 8, 8), 0.2857), ((8, 8, 8), 0.2877)],
+                         ids=str)
+def test_the_default_on_both_sides_of_the_pairs_smallest_mesh(shape, frac):
+    """256 and 257 cells, all regular; 1,534 and 1,541 with level jumps"""
+    f = I.uniform_forest(shape, 0)
+    if frac:
+        mask = np.zeros(len(f.level), bool)
+        mask[np.random.default_rng(3).permutation(len(f.level))[:round(frac * len(f.level))]] = True
+        f = I.refine(f, mask)
+    f1, m1 = _stepped(f, (576, 30), steps=2)
+    f2, m2 = _stepped(f, None, steps=2)
+    assert np.array_equal(f1, f2) and np.array_equal(m1, m2)
+
+
+def test_the_default_on_a_small_mesh_is_as_fast_as_one_launch():
+    """27 cells between walls: two launches take 1.8 times the one's time"""
+    import time
+    import torch
+    f = I.uniform_forest((3, 3, 3), 0, 1.0 / 3, WALLS)
+    a, b = _solver(f, 24, D.PREC_FP64), _solver(f, 24, D.PREC_FP64)
+    b.set_shape(576, 30, *b.get_shape()[2:])
+    best = [np.inf, np.inf]
+    for _ in range(20):
+        for k, s in enumerate((a, b)):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            s.step(100, cfl=0.5)
+            torch.cuda.synchronize()
+            best[k] = min(best[k], time.perf_counter() - t)
+    assert best[0] <= 1.25 * best[1]
