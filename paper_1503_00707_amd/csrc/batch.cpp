@@ -230,8 +230,7 @@ int dvm_batch_create(dvm_solver *const *solvers, int32_t n, double cfl, dvm_batc
     std::sort(b->groups.begin(), b->groups.end(), [](const Group &x, const Group &y) { return x.nh > y.nh; });
     for (auto &g : b->groups) {  // untouched shapes: runs and stores as for the group's cells together
         const dvm_solver *s = solvers[g.inst[0]];
-        const int64_t cells = int64_t(g.wg_end.back());
-        if (s->cfg_default) default_grouping(g.cfg, s->nh, cells, double(cells) * double(s->nv) * (s->fp64 ? 8 : 4));
+        if (s->cfg_default) default_grouping(g.cfg, s, int64_t(g.wg_end.back()));
     }
     size_t o = 0;
     for (auto &g : b->groups) {

@@ -52,7 +52,9 @@ hipError_t launch_pair(const dvm_solver *s, const StepArgs &a, const StepConfig 
 }
 }  // namespace
 
-void dvm::default_grouping(StepConfig &c, int nh, int64_t n, double state_bytes) {
+void dvm::default_grouping(StepConfig &c, const dvm_solver *s, int64_t n) {
+    const int nh = s->nh;
+    const double state_mb = double(n) * double(s->nv) * (s->fp64 ? 8 : 4) / double(1 << 20);
     // Consecutive cells share upwind rows, so each XCD takes runs of them.
     // Group 1 / 64 on 30,400 cells FP64: 16^3 nodes 700 / 565 us, 12^3 329 /
     // 294, 8^3 101 / 83; FP32 8^3, 243,200 cells: 421 / 365.  24^3 nodes: runs
@@ -67,8 +69,12 @@ void dvm::default_grouping(StepConfig &c, int nh, int64_t n, double state_bytes)
     // Non-temporal stores once the two state buffers exceed the 256 MB
     // Infinity Cache; below, the next step finds its rows there (FP64 16^3
     // nodes, 3,800 cells of 124 MB: 84 -> 75 us; 24^3, 1,590 cells of 176 MB:
-    // 153 us with, 177 without).
-    c.nt_store = state_bytes > 128.0 * (1 << 20);
+    // 153 us with, 177 without).  In FP32 from 12^3 nodes on also where a
+    // buffer is less than the XCDs' L2s (with / without, us: 24^3, 60 cells
+    // 13.9 / 14.5, 343 of 18 MB 18.4 / 19.7, 720 of 38 MB 26.7 / 26.4; 16^3,
+    // 720 of 11 MB 12.1 / 13.2, 2,184 of 34 MB 22.8 / 21.4; 12^3, 1,320 of 9 MB
+    // 12.6 / 14.0, 4,080 of 27 MB 22.7 / 21.4).
+    c.nt_store = state_mb > 128.0 || (!s->fp64 && nh >= 6 && state_mb < 24.0);
 }
 
 // On few cells the pair costs more than it gives: two launches one after the
@@ -173,7 +179,7 @@ int dvm_create_solver(const dvm_mesh *m, const dvm_params *p, dvm_solver **out) 
     // measured defaults per (precision, N); dvm_tune_set overrides them
     s->cfg.threads = thr;
     s->cfg.wpe = 0;
-    default_grouping(s->cfg, nh, s->n, double(s->n) * double(s->nv) * (fp64 ? 8 : 4));
+    default_grouping(s->cfg, s, s->n);
     if (nh == 12 && !fp64) {
         s->cfg.threads = 192;
         s->cfg.wpe = 31;

@@ -125,8 +125,8 @@ inline int list_shapes(const dvm_solver *s, int *threads, int *wpe, int cap) {
 bool runs_as_pair(const dvm_solver *s);
 // one step of the solver with shape cfg, a complete: one launch, the pair's two
 hipError_t launch_shape(const dvm_solver *s, const StepArgs &a, const StepConfig &cfg, hipStream_t st);
-// default runs of cells per XCD and kind of stores for n cells (state_bytes: one state buffer)
-void default_grouping(StepConfig &c, int nh, int64_t n, double state_bytes);
+// default runs of cells per XCD and kind of stores for n cells of the solver's kind
+void default_grouping(StepConfig &c, const dvm_solver *s, int64_t n);
 double solver_max_speed_sum(const dvm_solver *s);
 // f[cur] was replaced from outside the step (a remap): records, hybrid masks
 // and the moments buffer describe the new state
