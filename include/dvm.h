@@ -285,7 +285,7 @@ int dvm_tune_get(const dvm_solver *s, int32_t *threads, int32_t *wpe, int32_t *x
  * that such cells skip anyway.  (The shape (192, 21) of FP64 at 24^3 nodes,
  * the default there, is such a pair of launches by itself on meshes that fill
  * the device, with either setting, and computes the same step bitwise as
- * (576, 30), which small meshes and a batch take in its place.)
+ * one launch of 576 threads, which small meshes and a batch take in its place.)
  * threads_irr > 0 also
  * chooses the shape (threads per workgroup, waves-per-EU variant as listed by
  * dvm_tune_shapes) of the second launch; DVM_ERR_UNSUPPORTED if it does not

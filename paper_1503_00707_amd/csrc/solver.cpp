@@ -82,7 +82,9 @@ void dvm::default_grouping(StepConfig &c, const dvm_solver *s, int64_t n) {
 // us; 27 cells between walls 19 / 35, 209 cells with jumps 31.5 / 49.4, 581: 57
 // / 64, 1,057: 100 / 96, 1,452 between walls 112 / 121, 1,583: 147 / 142, 2,255:
 // 214 / 197).  Without other cells there is no second launch: 216 cells 20.0 /
-// 21.0, 343: 32.7 / 27.9.
+// 21.0, 343: 32.7 / 27.9.  The one launch holds five waves per EU where there is
+// more than a workgroup for each compute unit (729 cells between walls 60.7 us
+// against 63.5, 27 cells 16.9 against 16.7).
 bool dvm::runs_as_pair(const dvm_solver *s) {
     return s->n_reg > 0 && s->n > (s->n_reg == s->n ? 256 : 1536);
 }
@@ -92,7 +94,7 @@ hipError_t dvm::launch_shape(const dvm_solver *s, const StepArgs &a, const StepC
     if (runs_as_pair(s)) return launch_pair(s, a, cfg, ShapeId{576, 51}, st);
     StepConfig one = cfg;
     one.threads = kOneShape.threads;
-    one.wpe = kOneShape.wpe;
+    one.wpe = s->n > 256 ? 51 : kOneShape.wpe;
     return launch_step(s->fp64, a, one, st);
 }
 
