@@ -8,7 +8,7 @@
 // cells whose rows sit in LDS node-major ([node][cell]), so the gather of one
 // node for all cells of the tile is one contiguous vector read.  The LDS gathers
 // bound it (three of every trial, two thirds of their cycles bank conflicts, took
-// 931 us for 16^3 cells, 8^3 nodes, p = 1021 in FP64; 357 us now), so no trial
+// 931 us for 16^3 cells, 8^3 nodes, p = 1021 in FP64; 355 us now), so no trial
 // gathers what it need not:
 //   C runs over lists of the trials that have a gain term (61 % of them at 8^3),
 //     the nodes ordered by the length of their list so that the 64 nodes of a
@@ -28,6 +28,8 @@
 // The paper's own kernel runs one thread block per velocity node over all
 // cells, f stored velocity-major and transposed for the correction; here the
 // tables stream through L2 once per tile and f is never transposed.
+// Not free of scratch: the solve's 5 x 5 arrays lie there, and the shapes of
+// eight cells a thread spill some 30 of 128 registers (384 B a lane).
 #include <hip/hip_runtime.h>
 
 #include "step_impl.h"
@@ -90,7 +92,9 @@ __global__ __launch_bounds__(8 * NH * NH * NH / R * G) __attribute__((amdgpu_wav
     static_assert(!MAT || (R == 1 && CELLS <= 16), "one round, one tile of columns");
     // a node's row of the tile, padded to an odd number of 16-byte groups: rows
     // whose nodes differ modulo 16 start on different bank groups (the lists are
-    // arranged for that)
+    // arranged for that).  Rows of one group (FP32, four cells) take three all the
+    // same: 512 cells x 12^3 nodes 355 us, 371 with rows of one, 100 x 8^3 177
+    // against 183
     constexpr int RS = (CELLS * int(sizeof(F)) / 16 % 2 ? CELLS + 32 / int(sizeof(F)) : CELLS + 16 / int(sizeof(F)));
     constexpr int RB = CELLS + 2;
     constexpr size_t kTile = size_t(NV) * RS * sizeof(F), kB = MAT ? size_t(NV) * RB * 8 : 0;

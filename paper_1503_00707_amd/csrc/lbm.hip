@@ -69,8 +69,8 @@ __device__ __forceinline__ int face_kind(uint32_t meta, int f) { return int((met
 // the means of whole lists of them into LDS (kFineCap faces; a workgroup with
 // more of them forms each in its own lane), and a neighbour among the wave's
 // own 64 cells (about two thirds of them, in Morton order) is read from that
-// lane's registers.  D3Q19 FP32 on that octree: 95 -> 45 us a step, 253 MB
-// moved at 5.6 TB/s (a copy of that size reaches 7.0 TB/s here).
+// lane's registers.  D3Q19 FP32 on that octree: 95 -> 45 us a step, 248 MB past
+// the L2 at 5.8 TB/s (a copy of that size reaches 7.0 TB/s here).
 // BUF: the state fits 32-bit byte offsets, so every access is a raw buffer
 // access (per-lane 32-bit cell offset, the population's base as a scalar
 // offset) instead of a 64-bit address per lane.

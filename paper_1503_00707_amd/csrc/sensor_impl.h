@@ -661,7 +661,7 @@ __global__ __launch_bounds__(64) void k_mask_eff(const uint8_t *in, uint8_t *out
 // the tables and their sums, every lane the 5 x 6 elimination, a lane per
 // half-axis sum of the record.  Bound by latency: with a thread per cell the
 // same took 20.7 us on 16^3 cells x 8^3 nodes (64 wavefronts, 48 exponentials
-// and 100 divisions in one chain), 6.5 now.
+// and 100 divisions in one chain), 6.8 now.
 __global__ __launch_bounds__(64) void k_fluid_state(StepArgs a, HybArgs h) {
     __shared__ double2 tab[4][3][24];  // (g, 1 + d.phi part) per node; axis 0 carries C
     const int r = threadIdx.x >> 4, j = threadIdx.x & 15;
@@ -827,9 +827,10 @@ struct HybHook {
     // face `face`, uniform).  Up to three rounds a thread one code serves the
     // six faces and picks the octants by selects: with a copy per face the
     // cells next to fluid ones spent their time fetching instructions (hybrid
-    // channel, 26,100 cells x 12^3 nodes FP32: 233 -> 177 us with the sensor;
-    // 262,144 cells x 8^3: 597 -> 540).  At nine rounds (24^3 FP32) the selects
-    // cost more: 719 us with copies, 775 without.
+    // channel, 26,100 cells x 12^3 nodes FP32: 233 -> 177 us with the sensor,
+    // 193 with a cell's divisions in full; 262,144 cells x 8^3: 597 -> 540, 592).
+    // At nine rounds (24^3 FP32) the selects cost more: 719 us with copies, 775
+    // without.
     template <int FACE, typename F, int NH, int T>
     __device__ __forceinline__ void face_flux(const StepArgs &a, int64_t c, int face, const Regs<F, NH, T> &fo,
                                               double *red) const {
@@ -906,7 +907,9 @@ struct HybHook {
 // of the plain step.  A kinetic cell with no fluid face neighbour has nothing
 // to record and runs exactly the plain step's code (the reduced code when it
 // has no FINER or WALL face); one next to a fluid cell runs the full code with
-// the interface-flux hook.  All three compute the same step, bitwise.
+// the interface-flux hook.  All three compute the same step, bitwise.  One
+// kernel holds them all: at 24^3 FP32 the hook's copies make it spill 53 of its
+// 168 registers (208 B a lane), where the plain step's 155 fit.
 template <typename F, int NH, int T, int WPE, int FENCE, bool NT>
 __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(WPE, 8))) void k_step_hybrid(StepArgs a,
                                                                                                HybArgs h) {
@@ -1002,7 +1005,7 @@ __device__ __forceinline__ void fluid_face(const StepArgs &a, const HybArgs &h, 
 // and eight cells per one-wave workgroup: lane f < 6 takes face f, then lane
 // x < 5 adds the six faces' terms of moment x in face order.  With a thread
 // per cell the six faces' chains of dependent loads ran one after another:
-// 16.8 us on 16^3 cells, 4.9 now.
+// 16.8 us on 16^3 cells, 4.4 now.
 __global__ __launch_bounds__(64) void k_fluid_update(StepArgs a, HybArgs h) {
     __shared__ double terms[8][6][5];
     const int r = threadIdx.x >> 3, f = threadIdx.x & 7;
@@ -1076,7 +1079,8 @@ hipError_t hybrid_dispatch(const StepArgs &a, const HybArgs &h, hipStream_t st) 
     case 12:
         // FP64 rows do not fit the registers of 192 threads at three waves per
         // SIMD (394 spilled): the plain step's wide shape.  Channel, 8,000
-        // cells: 854 -> 576 us with the sensor (726 at five waves, 134 spilled).
+        // cells: 857 -> 582 us with the sensor (a quarter more at five waves, 134
+        // spilled).
         if constexpr (std::is_same<F, double>::value) {
             switch (a.g.nh) { DVM_HYB(12, 576, 3, 0) }
         } else {

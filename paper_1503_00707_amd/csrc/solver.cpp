@@ -16,11 +16,11 @@ namespace {
 // The FP64 default at 24^3 nodes, shape (192, 21): the regular cells with 192
 // threads at two waves per SIMD in one launch and the others with 576 at five
 // in a second.  Regular cells hold three times the loads in flight per wave
-// that way (27,000 of them: 1,962 -> 1,581 us); the correction pass over the
+// that way (27,000 of them: 2,014 -> 1,578 us); the correction pass over the
 // four rows behind a FINER face wants the wide workgroup (30,400 cells, 16 %
-// with such faces: one launch at 576 threads 2,555 us, at 192 threads 2,663,
-// two launches 2,317).  FP32 keeps one launch: 420,251 cells 12.5 ms against
-// 14.0.
+// with such faces: one launch at 576 threads 2,614 us, at 192 threads 4 %
+// more, two launches 2,351).  FP32 keeps one launch: 420,251 cells 12.5 ms
+// against 14.0.
 bool two_shapes(const dvm_solver *s, const StepConfig &cfg) {
     return has_two_shapes(s) && is_two_shapes(cfg.threads, cfg.wpe);
 }
@@ -58,8 +58,9 @@ void dvm::default_grouping(StepConfig &c, const dvm_solver *s, int64_t n) {
     // Consecutive cells share upwind rows, so each XCD takes runs of them.
     // Group 1 / 64 on 30,400 cells FP64: 16^3 nodes 700 / 565 us, 12^3 329 /
     // 294, 8^3 101 / 83; FP32 8^3, 243,200 cells: 421 / 365.  24^3 nodes: runs
-    // of 32, whose rows fit the XCD's L2 (FP32, 420,251 cells, 512 / 128 / 32
-    // / 8: 12.51 / 12.37 / 12.31 / 12.73 ms; 3,800 cells, 512 / 16: 175 / 141
+    // of 32, by time alone (FP32, 420,251 cells, 512 / 128 / 32 / 8: 12.51 /
+    // 12.37 / 12.31 / 12.73 ms, though the shorter runs read more past the L2:
+    // 996,150 cells 122 GB at 512, 138 at 32; 3,800 cells, 512 / 16: 175 / 141
     // us; FP64, 30,400 cells, 64 / 32: 2,340 / 2,317 us).  A round over the
     // XCDs has to fit the mesh: at most n / 8.
     int64_t g = nh == 12 ? 32 : 64;

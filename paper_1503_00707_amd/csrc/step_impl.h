@@ -1076,11 +1076,12 @@ __device__ __forceinline__ void transport_muscl(Regs<F, NH, T> &fo, const CellVi
 // compute unit.  Walking the neighbours' records per octant and axis instead
 // cost 24 chains of dependent scalar loads a cell, paid by every cell with a
 // level jump within two hops (31 % to 95 % of the cells of these meshes):
-//   Mach-2 sphere (58,768 cells, 24^3, FP32)      5.80 -> 4.38 ms, 4.17 in
-//                                                 runs of 32 cells per XCD
-//   octree, 40 % refined (30,400 cells, 24^3)     5.76 -> 3.56 ms, 3.50
-//   the same in FP64 (10,427 cells)               3.40 -> 2.13 ms
+//   Mach-2 sphere (58,768 cells, 24^3, FP32)      5.79 -> 4.29 ms
+//   octree, 40 % refined (30,400 cells, 24^3)     5.76 -> 3.56 ms
+//   the same in FP64 (10,427 cells)               3.40 -> 2.12 ms
 // (with them the median instruction in minmod, 8 % where no cell has a jump).
+// At 24^3 FP32 it does not quite fit the 72 registers: 8 spill, 36 B a lane,
+// which a launch pays with 1.3 times the state's bytes written.
 // Measured and not kept: the same code for every cell at 576 and at 896 threads
 // (no jumps: 2.7 ms against 1.6), the axes one at a time with the next one
 // prefetched (5.0 ms on the octree), two launches, one per kind of cell (3.7
