@@ -497,6 +497,7 @@ int dvm_adapt_tables(dvm_solver *s, const uint8_t *level, const int32_t *ijk, vo
     if (e != hipSuccess) return hip_fail(e, "adapt tables");
     if (bad) return fail(DVM_ERR_UNBALANCED, "the leaf list is not a 2:1-balanced partition");
     s->n_reg = n_reg;
+    if (s->cfg_default) default_grouping(s->cfg, s, s->n, s->state_bytes());  // whether the step is a pair of launches
     for (int f = 0; f < 6; ++f) m->n_faces[f] = int64_t(counts[f]);
     if (s->tables_pending) {
         s->tables_pending = false;

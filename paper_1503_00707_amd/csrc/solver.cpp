@@ -52,9 +52,8 @@ hipError_t launch_pair(const dvm_solver *s, const StepArgs &a, const StepConfig 
 }
 }  // namespace
 
-void dvm::default_grouping(StepConfig &c, const dvm_solver *s, int64_t n) {
+void dvm::default_grouping(StepConfig &c, const dvm_solver *s, int64_t n, double state_bytes) {
     const int nh = s->nh;
-    const double state_mb = double(n) * double(s->nv) * (s->fp64 ? 8 : 4) / double(1 << 20);
     // Consecutive cells share upwind rows, so each XCD takes runs of them.
     // Group 1 / 64 on 30,400 cells FP64: 16^3 nodes 700 / 565 us, 12^3 329 /
     // 294, 8^3 101 / 83; FP32 8^3, 243,200 cells: 421 / 365.  24^3 nodes: runs
@@ -62,20 +61,31 @@ void dvm::default_grouping(StepConfig &c, const dvm_solver *s, int64_t n) {
     // 12.37 / 12.31 / 12.73 ms, though the shorter runs read more past the L2:
     // 996,150 cells 122 GB at 512, 138 at 32; 3,800 cells, 512 / 16: 175 / 141
     // us; FP64, 30,400 cells, 64 / 32: 2,340 / 2,317 us).  A round over the
-    // XCDs has to fit the mesh: at most n / 8.
-    int64_t g = nh == 12 ? 32 : 64;
+    // XCDs has to fit the mesh: at most n / 8 (4,200 meshes of 40 to 4,000
+    // cells, all grids: 6 % faster than without runs, 4 % of them slower by more
+    // than 1.5 %; n / 16 and n / 32 worse).  Below 100 cells every cell has a
+    // compute unit, and runs gain 1 % or lose up to 10: none.  FP64 24^3 in one
+    // launch of few rounds over the compute units: 64 (512 to 1,536 cells, 900
+    // meshes: 32 takes 2 % less on average, but up to 30 % more).
+    const bool few = has_two_shapes(s) && !runs_as_pair(s) && n >= 512;
+    int64_t g = n < 100 ? 1 : nh == 12 && !few ? 32 : 64;
     g = std::min(g, std::max<int64_t>(1, n / 8));
     c.xcd_group = 1;
     while (2 * c.xcd_group <= g) c.xcd_group *= 2;
-    // Non-temporal stores once the two state buffers exceed the 256 MB
-    // Infinity Cache; below, the next step finds its rows there (FP64 16^3
-    // nodes, 3,800 cells of 124 MB: 84 -> 75 us; 24^3, 1,590 cells of 176 MB:
-    // 153 us with, 177 without).  In FP32 from 12^3 nodes on also where a
-    // buffer is less than the XCDs' L2s (with / without, us: 24^3, 60 cells
-    // 13.9 / 14.5, 343 of 18 MB 18.4 / 19.7, 720 of 38 MB 26.7 / 26.4; 16^3,
-    // 720 of 11 MB 12.1 / 13.2, 2,184 of 34 MB 22.8 / 21.4; 12^3, 1,320 of 9 MB
-    // 12.6 / 14.0, 4,080 of 27 MB 22.7 / 21.4).
-    c.nt_store = state_mb > 128.0 || (!s->fp64 && nh >= 6 && state_mb < 24.0);
+    // Stores: non-temporal once the two state buffers exceed the 256 MB Infinity
+    // Cache.  Below that plain ones leave the next step its rows there, but what
+    // they write back is paid for when other states step in between.  One state
+    // over and over, non-temporal / plain, then three in turn, us: FP64 16^3,
+    // 3,800 cells, 84 / 75; FP32 12^3, 12,167 cells, 56.4 / 47.8, 56.2 / 60.3;
+    // 24^3, 1,728 cells, 57.7 / 52.0, 58.0 / 61.9; 16^3, 5,832 cells, 50.6 /
+    // 46.5, 51.1 / 55.5; FP64 24^3, 818 cells, 93.4 / 87.6, 94.5 / 102.1.  The
+    // last two had non-temporal stores at every size and keep them (in turn they
+    // were up to 6 % slower without; FP64 24^3 below 40 MiB is not: 343 cells
+    // 30.5 / 28.0).  FP32 from 12^3 on is also better off with them where a
+    // buffer is less than the XCDs' L2s (24^3, 343 cells of 18 MB, 18.4 / 19.7;
+    // 12^3, 1,320 of 9 MB, 12.6 / 14.0).
+    const double mb = state_bytes / double(1 << 20);
+    c.nt_store = mb > 128.0 || (s->fp64 ? nh == 12 && mb > 40.0 : nh == 8 || (nh >= 6 && mb < 24.0));
 }
 
 // On few cells the pair costs more than it gives: two launches one after the
@@ -182,7 +192,6 @@ int dvm_create_solver(const dvm_mesh *m, const dvm_params *p, dvm_solver **out) 
     // measured defaults per (precision, N); dvm_tune_set overrides them
     s->cfg.threads = thr;
     s->cfg.wpe = 0;
-    default_grouping(s->cfg, s, s->n);
     if (nh == 12 && !fp64) {
         s->cfg.threads = 192;
         s->cfg.wpe = 31;
@@ -245,6 +254,7 @@ int dvm_create_solver(const dvm_mesh *m, const dvm_params *p, dvm_solver **out) 
             if (irregular == (pass == 1)) s->sel_host.push_back(uint32_t(c));
             if (pass == 0 && !irregular) ++s->n_reg;
         }
+    default_grouping(s->cfg, s, s->n, s->state_bytes());
     // the second launch's shape: one with a full kernel, which the pair has not
     s->cfg_irr = s->cfg;
     if (two_shapes(s, s->cfg)) {

@@ -69,6 +69,7 @@ struct dvm_solver {
     void *gin() const { return ws + off_gin; }
     void *m1() const { return ws + off_m1; }
     bool korobov() const { return p.collision == DVM_COLL_KOROBOV; }
+    double state_bytes() const { return double(n) * double(nv) * (fp64 ? 8 : 4); }
     double *den() const { return reinterpret_cast<double *>(ws + off_den); }
     int *flag() const { return reinterpret_cast<int *>(ws + off_flag); }
     double *partials() const { return reinterpret_cast<double *>(ws + off_part); }
@@ -125,8 +126,9 @@ inline int list_shapes(const dvm_solver *s, int *threads, int *wpe, int cap) {
 bool runs_as_pair(const dvm_solver *s);
 // one step of the solver with shape cfg, a complete: one launch, the pair's two
 hipError_t launch_shape(const dvm_solver *s, const StepArgs &a, const StepConfig &cfg, hipStream_t st);
-// default runs of cells per XCD and kind of stores for n cells of the solver's kind
-void default_grouping(StepConfig &c, const dvm_solver *s, int64_t n);
+// default runs of cells per XCD for n cells of the solver's kind, and kind of
+// stores (state_bytes: one state buffer of every instance that steps together)
+void default_grouping(StepConfig &c, const dvm_solver *s, int64_t n, double state_bytes);
 double solver_max_speed_sum(const dvm_solver *s);
 // f[cur] was replaced from outside the step (a remap): records, hybrid masks
 // and the moments buffer describe the new state
