@@ -811,8 +811,11 @@ struct MusclWords {
     __device__ __forceinline__ F ifar(int f) const { return factor(w1, f * 2 * W); }
     __device__ __forceinline__ F inear(int f) const { return factor(w1, f * 2 * W + W); }
 };
-constexpr uint32_t kUp4 = 1, kNear4 = 2;                // FINER face; COARSER face
+// A cell without a slope (it touches a wall) needs no row beyond itself, on either
+// side of a face: its bits stay clear, and one row stands in that a factor of 0 drops.
+constexpr uint32_t kUp4 = 1, kNear4 = 2;                // FINER face; COARSER face to a cell with a slope
 constexpr uint32_t kFar4 = 4;                           // << k: the far side of up[f][k] is four rows
+constexpr uint32_t kDn4 = 64;                           // FINER face of a cell with a slope
 
 // Threads 0..23 (face f = t / 4, cell k = t % 4 across it) fill the table: the
 // records of all the neighbours are read side by side, two dependent trips to
@@ -838,14 +841,15 @@ __device__ __forceinline__ void muscl_table(MusclTab<F> &tab, const StepArgs &a,
                    : ty == DVM_FACE_WALL ? reinterpret_cast<uint64_t>(a.wall_m1)
                                          : row(x);  // OUTFLOW: zero gradient, the cell itself
     if (k == 0) tab.iup[f] = inv(ty, h);
-    uint32_t flag = finer ? kUp4 : ty == DVM_FACE_COARSER ? kNear4 : 0;
+    uint32_t flag = finer ? kUp4 | (rec.flags & 1 ? 0 : kDn4) : 0;
     if (!inside) {
         tab.far[f][0][0] = tab.up[f][0];
         tab.hu[f][0] = F(0);
         tab.ifar[f][0] = tab.inear[f] = F(1.0 / h);
     } else {
         const DevCell &u = a.cells[x];
-        const int tf = u.type[f];
+        const bool slope = !(u.flags & 1);
+        const int tf = slope ? u.type[f] : DVM_FACE_OUTFLOW;
         const double hx = a.h0 / double(1 << u.level);
         if (tf == DVM_FACE_FINER) {
             flag |= kFar4 << k;
@@ -856,11 +860,13 @@ __device__ __forceinline__ void muscl_table(MusclTab<F> &tab, const StepArgs &a,
                                                        : row(x);  // OUTFLOW, WALL: its own value
         }
         tab.ifar[f][k] = inv(tf, hx);
-        tab.hu[f][k] = (u.flags & 1) ? F(0) : F(0.5 * hx);
+        tab.hu[f][k] = slope ? F(0.5 * hx) : F(0);
         if (k == 0) {
             tab.inear[f] = inv(u.type[f ^ 1], hx);
-            if (ty == DVM_FACE_COARSER)
+            if (slope && ty == DVM_FACE_COARSER) {
+                flag |= kNear4;
                 for (int j = 0; j < 4; ++j) tab.near[f][j] = row(u.nbr[f ^ 1][j]);
+            }
         }
     }
     // the four lanes of a FINER face (consecutive, all here) put their bits together
@@ -1117,8 +1123,7 @@ __device__ __forceinline__ void transport_muscl_jumps(Regs<F, NH, T> &fo, const 
     for (int o = 0; o < 8; ++o) {
         const uint32_t so = uint32_t(o) * uint32_t(L::B * sizeof(F));
         int fu[3];
-        uint32_t fl[3];  // kUp4 | kNear4 | kFar4.. of the upwind face; kDn4: FINER downwind
-        constexpr uint32_t kDn4 = 1u << 8;
+        uint32_t fl[3];  // flags of the upwind face, but kDn4 of the downwind one
         F v[S], up[2][S], dn[2][S], fr[2][S];  // two axes' rows in flight at a time
 #pragma unroll
         for (int q = 0; q < S; ++q) v[q] = bld<F>(own, voff, so + q * kRound);
@@ -1126,7 +1131,7 @@ __device__ __forceinline__ void transport_muscl_jumps(Regs<F, NH, T> &fo, const 
             const int x = b & 1;
             fu[b] = 2 * b + 1 - ((o >> (2 - b)) & 1);  // a positive component enters through the low face
             const int fd = fu[b] ^ 1;
-            fl[b] = words.flag(fu[b]) | ((words.flag(fd) & kUp4) << 8);
+            fl[b] = (words.flag(fu[b]) & ~kDn4) | (words.flag(fd) & kDn4);
             // values made of several rows are read further down: nothing here
             const Rsrc ru = rsrc(words.up(fu[b]), fl[b] & kUp4 ? 0 : kRow);
             const Rsrc rd = rsrc(words.up(fd), fl[b] & kDn4 ? 0 : kRow);
